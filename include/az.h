@@ -228,9 +228,11 @@ int az_net_moves(const az_net* net);
 
 /* Kernel tiling used by az_eval_batch.  0: chosen from B and the dtype
  * (default); 1 (large): four boards per workgroup (F = 64, 128) or two
- * (F = 256), one workgroup per compute unit; 2 (small): one board per
- * workgroup; 3 (medium, F = 64 and 128 only): two boards per workgroup, two
- * workgroups per compute unit.  The deployed network has two: 1, one wave per
+ * (F = 256), one workgroup per compute unit; 2 (small): the fewest boards per
+ * workgroup that place the batch on the compute units in one round: one up to a
+ * board per compute unit, then two, then as the large tiling; 3 (medium, F = 64
+ * and 128 only): two boards per workgroup, two workgroups per compute unit (one
+ * for AZ_BF16 with F = 128).  The deployed network has two: 1, one wave per
  * board (several boards per compute unit); 2, four waves per board (one board
  * per compute unit, for small batches).  Every tiling computes bitwise the
  * same results.  AZ_F32 has a single tiling and accepts only 0.  Returns

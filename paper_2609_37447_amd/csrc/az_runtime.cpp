@@ -3,18 +3,19 @@
 //
 // Packed weight streams (MFMA dtypes).  A 3x3 conv with C' input channels
 // (the stem pads 20 -> 32) is the GEMM D[ch][sq] = sum_k W[ch][k] X[k][sq] with
-// k = tap * C' + c, tap = 3*dy + dx.  With KS the reduction length of one MFMA
+// tap = 3*dy + dx; a K step is KS input channels of one tap, and the steps run
+// (dx, channel step, dy) as the kernel's K loop does.  With KS the reduction length of one MFMA
 // (bf16 16, int8 32, fp8 64) the stream holds, for every K step s and every
 // 32-channel block mb, one 64-lane fragment; lane l carries
-//   W[mb*32 + l%32][s*KS + (KS/2)*(l/32) + t],  t = 0 .. KS/2-1,
+//   W[mb*32 + l%32][cs*KS + (KS/2)*(l/32) + t][tap],  t = 0 .. KS/2-1,
 // contiguously (16 bytes for bf16 and int8, 32 for fp8), so that a wave loads
 // a fragment with one fully coalesced read.  The B-operand (activation) lanes
 // use the same k slots, so the pairing of A and B k values matches by
 // construction.  Order: stem (bf16), then the 2*blocks residual convs, then
 // the head: 96 rows (policy planes, value 1x1 conv row, zero rows), K = F.
 //
-// The deployed network (from-to policy, WDL value, global pooling) pads the
-// stem to 64 input channels, packs the second convolution of a pooling block
+// The deployed network (from-to policy, WDL value, global pooling) orders its K
+// steps tap by tap (k = tap * C' + c), pads the stem to 64 input channels, packs the second convolution of a pooling block
 // ([F][Fr][3][3]) with zero weights for input channels Fr..F-1, and packs its
 // heads as described in az_dep_kernel.h.
 #include "../../include/az.h"
@@ -245,8 +246,9 @@ float e4m3_value(uint8_t c) {
 
 enum Kind { K_BF16 = 0, K_I8 = 1, K_F8 = 2 };
 
-// Packs a 3x3 conv W[F][Cin][3][3] (padded to Cp input channels) into A fragments.
-void pack_conv(const float* W, const float* wscale, int F, int Cin, int Cp, Kind kind,
+// Packs a 3x3 conv W[F][Cin][3][3] (padded to Cp input channels) into A fragments,
+// tap by tap, or (rows) with the K steps ordered (dx, channel step, dy).
+void pack_conv(const float* W, const float* wscale, int F, int Cin, int Cp, Kind kind, bool rows,
                std::vector<uint8_t>& out) {
   const int KS = kind == K_BF16 ? 16 : kind == K_I8 ? 32 : 64;
   const int es = kind == K_BF16 ? 2 : 1;
@@ -254,13 +256,16 @@ void pack_conv(const float* W, const float* wscale, int F, int Cin, int Cp, Kind
   const size_t base = out.size();
   out.resize(base + (size_t)S * nMB * 64 * FB);
   uint8_t* o = out.data() + base;
-  for (int s = 0; s < S; ++s)
+  const int cpt = Cp / KS;  // channel steps of a tap
+  for (int s = 0; s < S; ++s) {
+    const int tap = rows ? 3 * (s % 3) + s / (3 * cpt) : s / cpt;
+    const int cs = rows ? s / 3 % cpt : s % cpt;
     for (int mb = 0; mb < nMB; ++mb)
       for (int l = 0; l < 64; ++l) {
         const int ch = mb * 32 + l % 32;
         uint8_t* dst = o + ((size_t)(s * nMB + mb) * 64 + l) * FB;
         for (int t = 0; t < half; ++t) {
-          const int k = s * KS + half * (l / 32) + t, tap = k / Cp, c = k % Cp;
+          const int c = cs * KS + half * (l / 32) + t;
           const float v = c < Cin ? W[((size_t)ch * Cin + c) * 9 + tap] : 0.0f;
           if (kind == K_BF16) {
             const uint16_t h = bf16_rne(v);
@@ -273,6 +278,7 @@ void pack_conv(const float* W, const float* wscale, int F, int Cin, int Cp, Kind
           }
         }
       }
+  }
 }
 
 void pack_head(const BlobView& v, int F, int P, std::vector<uint8_t>& out) {
@@ -352,11 +358,6 @@ std::vector<uint32_t> fromto_actions() {
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Measured on MI355X (20x128 and 24x256 networks): one board per workgroup wins
-// below a few hundred boards; at 1024 boards the four-board large tiling wins
-// for bf16 and fp8, and the two-board medium tiling (two workgroups per compute
-// unit) ties with it for int8.
-//
 // Deployed network: the tiling with the shorter estimated time, rounds x time
 // per round.  A round is one board per compute unit with four waves per board,
 // and four (int8) or three (bf16, LDS-bound) boards per compute unit with one
@@ -376,16 +377,27 @@ int choose_tiling(const az_net* n, int B) {
   if (is_deployed(n->spec)) return choose_dep_tiling(n, B);
   const int F = n->spec.filters;
   if (B < 512) return 2;
-  // Measured on 20x128 (us per batch, large / one-board / medium tiling):
-  // int8 768 boards 293 / 283 / 295, 896 boards 303 / 342 / 311, 1,024 boards
-  // 327 / 368 / 338; bf16 640 boards 487 / 459 / 458, 768 boards 495 / 510 / 512.
-  // fp8: 640 boards 335 / 293 / 314, 768 boards 337 / 310 / 326, 896 boards
-  // 340 / 384 / 337, 1,024 boards 350 / 402 / 357.
   if (n->dtype == AZ_INT8) return B <= 768 ? 2 : 1;
   if (n->dtype == AZ_BF16) return B >= 768 ? 1 : 2;
   if (B <= 768) return 2;
   if (B >= 1024) return 1;
   return az_mfma_tiling_valid(F, 3) ? 3 : 1;
+}
+
+// The kernel a move-plane network's tiling runs for a batch of B.  The small tiling
+// takes the fewest boards per workgroup that place the batch on the compute units
+// in one round: a second workgroup on a compute unit costs more than a second
+// board in the first one, which shares its weight stream.  Measured on 20x128 with
+// 256 compute units (us per batch; one / two / four boards per workgroup):
+//   int8  256 boards 97 / 136 / 232, 288 boards 148 / 136 / 233, 512 boards
+//         181 / 161 / 234, 576 boards 246 / 249 / 234, 768 boards 270 / 262 / 235
+//   bf16  256 boards 162 / 210 / 380, 288 boards 251 / 211 / 380, 512 boards
+//         312 / 280 / 382, 576 boards 414 / 481 / 383
+//   20x256 int8 (one / two boards) 256 boards 310 / 428, 320 boards 563 / 428
+int choose_kernel(const az_net* n, int B) {
+  const int t = choose_tiling(n, B), F = n->spec.filters;
+  if (t != 2 || B <= n->cus) return t;
+  return az_mfma_tiling_valid(F, 3) && B <= 2 * n->cus ? 3 : 1;
 }
 
 }  // namespace
@@ -553,12 +565,12 @@ int az_net_load(const az_layer_spec* spec_in, const float* weights, size_t n_wei
             h[((size_t)rb * F + f) * 8 + j] = row < P ? v.pol_w[(size_t)row * F + f] : row == P ? v.val_w[f] : 0.0f;
           }
     } else {
-      pack_conv(v.stem_w, nullptr, F, Cin, dep ? AZ_DEP_MAX_IN_PLANES : 32, K_BF16, stem);
+      pack_conv(v.stem_w, nullptr, F, Cin, dep ? AZ_DEP_MAX_IN_PLANES : 32, K_BF16, !dep, stem);
       const Kind kind = dtype == AZ_BF16 ? K_BF16 : dtype == AZ_INT8 ? K_I8 : K_F8;
       for (int n = 0; n < 2 * NB; ++n) {
         // the second convolution of a pooling block reads the Fr regular channels
         const int cin = (n % 2 == 1 && is_pool_block(s, n / 2)) ? Fr : F;
-        pack_conv(v.w[n], quant ? w_scales + (size_t)n * F : nullptr, F, cin, F, kind, tower);
+        pack_conv(v.w[n], quant ? w_scales + (size_t)n * F : nullptr, F, cin, F, kind, !dep, tower);
       }
       if (!dep) pack_head(v, F, P, head);
       if (quant) {
@@ -772,7 +784,7 @@ int az_eval_batch_wdl(az_net* net, const float* planes, const uint8_t* legal, in
   else if (net->dtype == AZ_F32)
     e = az_launch_f32(net->dn, planes, legal, B, policy, value, s);
   else
-    e = az_launch_mfma(net->dtype, choose_tiling(net, B), net->dn, planes, legal, B, policy, value, s);
+    e = az_launch_mfma(net->dtype, choose_kernel(net, B), net->dn, planes, legal, B, policy, value, s);
   if (cur != net->device) (void)hipSetDevice(cur);
   if (e != hipSuccess) return hip_fail(e, "kernel launch");
   return AZ_OK;

@@ -268,6 +268,32 @@ def test_tilings_agree_bitwise(wname, dtype):
         assert np.array_equal(P, outs[0][0]) and np.array_equal(V, outs[0][1])
 
 
+@pytest.mark.parametrize("filters,dtype", [(64, "int8"), (128, "bf16"), (128, "int8"), (256, "bf16")])
+def test_small_tiling_board_counts(filters, dtype):
+    # The small tiling takes one board per workgroup up to a board per compute
+    # unit, then two, then four: around each step of that rule every row equals
+    # the large tiling's bit for bit, and sampled rows equal the oracle's (the
+    # edges of the batch and of the workgroups at the steps).
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    shape = azgen.NetShape(in_planes=20, blocks=1, filters=filters, policy_planes=73, value_hidden=64)
+    blob = azgen.make_weights(shape, 910 + filters, alpha_fold=True, bf16=True)
+    _scale_fc2(shape, blob, 1.0 / 8)
+    ws = acs = None
+    if dtype == "int8":
+        ws = O.weight_scales(shape, blob, dtype)
+        acs = O.act_scales_from_absmax(O.calibrate_absmax(shape, blob, _shape_inputs(shape, 64, 99)[0]), dtype)
+    planes, legal = _shape_inputs(shape, 2 * cus + 3, 31)
+    for B in (cus, cus + 1, 2 * cus, 2 * cus + 3):
+        _print(f"case small tiling {filters} {dtype} B={B}")
+        P2, V2 = H.gpu_eval(shape, blob, dtype, planes[:B], legal[:B], ws, acs, tiling=2)
+        P1, V1 = H.gpu_eval(shape, blob, dtype, planes[:B], legal[:B], ws, acs, tiling=1)
+        assert np.array_equal(P2, P1) and np.array_equal(V2, V1)
+        rows = np.array([0, 1, 2, 3, 5, B // 2, B - 4, B - 3, B - 2, B - 1])
+        Pr, Vr = H.oracle_eval(shape, blob, dtype, planes[rows], legal[rows], ws, acs)
+        H.compare(P2[rows], V2[rows], Pr, Vr, dtype)
+
+
 def test_refit_equal_then_unequal_scales():
     # Loading a handle with all-equal quantisation scales and then a new handle
     # with unequal ones must give the quantised oracle's answer both times, every
