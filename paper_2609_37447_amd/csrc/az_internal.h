@@ -20,7 +20,7 @@ struct AzDevNet {
   float act_cap;     // +inf when the activation is a plain ReLU
   float head_scale;  // value of one code of the final tower tensor (1 for float nets)
   // MFMA dtypes: A-fragment streams (see az_runtime.cpp for the order).
-  // AZ_F32: canonical fp32 arrays.
+  // AZ_F32: A fragments of the weights' three bf16 parts.
   const void* stem_w;
   const void* tower_w;
   const void* head_w;

@@ -1,215 +1,357 @@
-// Fused policy/value network evaluation in fp32 on the vector ALUs.
+// Fused policy/value network evaluation in fp32 (AZ_F32), on the bf16 matrix
+// cores.
 //
-// One workgroup of 256 threads evaluates one board: the activations live in
-// LDS as [channel][square] fp32.  Each thread owns one square and accumulates
-// eight output channels at a time in registers, so every LDS read of an input
-// value feeds eight FMAs; the eight weights of one (input channel, tap) are one
-// contiguous, wave-uniform 32-byte load (weights packed [F/8][C][9][8]), and the
-// next input channel's weights are loaded while the current ones are used.
-// This is the full-precision path (AZ_F32); it is sized for small networks and
-// small batches, where the network is too small to feed the matrix cores.
+// Every fp32 operand x is the exact sum of three bf16 parts, x = h + m + l with
+// h = bf16(x), m = bf16(x - h), l = x - h - m (8 + 8 + 8 significant bits), and a
+// product w * x is taken as the six part products of weight 2^-16 or more: hw hx
+// into one fp32 accumulator, lw hx, hw lx, mw mx, mw hx and hw mx into another.
+// Each is exact in fp32; what is left out is below 2^-25 of the product, under the
+// rounding of one fp32 multiply-add, and the leading accumulator is rounded once
+// per 32 channels where the multiply-add chain was once per channel.  Distance from
+// float64 (2-norm, policy / value; in brackets fp32 multiply-adds on the vector
+// ALUs, which this replaces): 2x32 1.3e-7 / 2.1e-7 (3.6e-7 / 4.1e-7), 20x128 3.2e-7 /
+// 9.2e-7 (7.3e-7 / 2.3e-6), 2x256 2.0e-7 / 5.6e-7 (5.9e-7 / 1.2e-6).  With all six
+// in one accumulator it was no better than the chain.  The bf16 instruction runs at
+// 16 times the rate of the fp32 one, so six products cost 0.38 of it.
+//
+// One workgroup of eight waves (two per SIMD, to cover each other's latencies)
+// evaluates one board.  A convolution is an implicit GEMM of 16x16 blocks: 16
+// output channels by 16 squares, block b = rows b and b + 4 of the board, so that
+// the LDS fragments of one horizontal tap and channel step serve all three
+// vertical taps (block b's neighbour rows are block b +- 1).  A wave owns MB
+// channel blocks x NB square blocks, chosen so that one pass covers the layer:
+// 1 x 1 up to 32 filters, 1 x 2 up to 64, 1 x 4 up to 128, 2 x 4 up to 256.
+//
+// LDS holds one activation buffer: [square slot][part h, m, l][channel].  Slots
+// are 9 to a row with zero rows above and below the board and one zero column
+// between rows, so no tap needs a bounds check; a slot is an odd number of
+// 16-byte units.  A layer keeps its outputs in registers until every wave has
+// read the buffer, then overwrites it; the residual stream stays in registers in
+// fp32.  Weights stream from L2 through a ring of the three vertical taps.
+//
+// What bounds it: the six products (27.6k MFMA cycles a 128-filter convolution on
+// the one compute unit a board has, 0.46 ms for 20x128) and, on small networks, the
+// latency of the layers' chain.  20x128, 64 boards: 13.5 ms -> 0.68 ms; 2x32, 16
+// boards: 100 -> 20 us; 1,024 boards: 343 -> 79 us; 2x256, 16 boards: 5.7 -> 0.27 ms.
 #include "az_internal.h"
+#include "az_mfma_common.h"
 
 #include <math.h>
 
 namespace {
 
-constexpr int NT = 256;
-// LDS staging area for one convolution's weights (used when they fit), at most
-// this many floats and never past the 160 KB of LDS
-constexpr int WSTAGE_FLOATS = 12 * 1024;
-constexpr int LDS_FLOATS = 160 * 1024 / 4;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
-__device__ __forceinline__ float act_fn(float y, float cap) { return fminf(fmaxf(y, 0.0f), cap); }
+constexpr int NW = 8, NT = 64 * NW;
+constexpr int SLOTS = 91;  // (8 + 2) rows x 9 columns, and the last row's right neighbour
+constexpr int CELLS = AZ_MAX_POLICY * 64;
 
-// out[f][sq] = act(bias[f] + sum_{c,tap} W[f][c][tap] * in[c][sq + tap] (+ out[f][sq]));
-// W8 is [F/8][C][9][8]; out-of-board taps read zero.
-__device__ void conv3x3_f32(const float* in, int C, const float* __restrict__ W8g,
-                            const float* __restrict__ bias, float* out, int F, bool residual,
-                            float cap, float* wst, int wcap) {
-  const int tid = threadIdx.x, sq = tid & 63;
-  // weights that fit are copied to LDS first (coalesced), so the loop below
-  // reads them with LDS latency instead of L2 latency
-  const float* W8 = W8g;
-  if (F * C * 9 <= wcap) {
-    const float4* src = reinterpret_cast<const float4*>(W8g);
-    float4* dst = reinterpret_cast<float4*>(wst);
-    for (int i = tid; i < F * C * 9 / 4; i += NT) dst[i] = src[i];
-    __syncthreads();
-    W8 = wst;
-  }
-  const int g = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int r = sq >> 3, c = sq & 7;
-  int nb[9];
-  bool ok[9];
-#pragma unroll
-  for (int t = 0; t < 9; ++t) {
-    const int rr = r + t / 3 - 1, cc = c + t % 3 - 1;
-    ok[t] = (unsigned)rr < 8u && (unsigned)cc < 8u;
-    nb[t] = ok[t] ? rr * 8 + cc : sq;
-  }
-  for (int fb = g; fb < F / 8; fb += NT / 64) {
-    const float4* w = reinterpret_cast<const float4*>(W8 + (size_t)fb * C * 72);
-    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    float4 wc[18];
-#pragma unroll
-    for (int k = 0; k < 18; ++k) wc[k] = w[k];
-    for (int ci = 0; ci < C; ++ci) {
-      float4 wn[18];
-      const float4* wnext = w + (size_t)(ci + 1 < C ? ci + 1 : ci) * 18;
-#pragma unroll
-      for (int k = 0; k < 18; ++k) wn[k] = wnext[k];
-      const float* x = in + ci * 64;
-#pragma unroll
-      for (int t = 0; t < 9; ++t) {
-        const float xv = ok[t] ? x[nb[t]] : 0.0f;
-        const float4 a = wc[2 * t], b = wc[2 * t + 1];
-        acc[0] = fmaf(a.x, xv, acc[0]);
-        acc[1] = fmaf(a.y, xv, acc[1]);
-        acc[2] = fmaf(a.z, xv, acc[2]);
-        acc[3] = fmaf(a.w, xv, acc[3]);
-        acc[4] = fmaf(b.x, xv, acc[4]);
-        acc[5] = fmaf(b.y, xv, acc[5]);
-        acc[6] = fmaf(b.z, xv, acc[6]);
-        acc[7] = fmaf(b.w, xv, acc[7]);
-      }
-#pragma unroll
-      for (int k = 0; k < 18; ++k) wc[k] = wn[k];
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int f = fb * 8 + j;
-      float y = acc[j] + bias[f];
-      if (residual) y += out[f * 64 + sq];
-      out[f * 64 + sq] = act_fn(y, cap);
-    }
-  }
-  __syncthreads();
+struct Split { bf16x8 h, m, l; };
+
+// x = h + m + l.  A part of a non-finite x is x itself, the others zero.
+__device__ __forceinline__ void split3(float x, uint32_t& h, uint32_t& m, uint32_t& l) {
+  h = bf16_bits(x);
+  const float hf = __uint_as_float(h << 16);
+  const float r = fabsf(hf) < INFINITY ? x - hf : 0.0f;
+  m = bf16_bits(r);
+  l = bf16_bits(r - __uint_as_float(m << 16));
 }
 
-__device__ float block_reduce(float v, bool is_max, float* scratch) {
-  for (int o = 32; o > 0; o >>= 1) {
-    const float u = __shfl_xor(v, o);
-    v = is_max ? fmaxf(v, u) : v + u;
-  }
-  const int tid = threadIdx.x;
-  if ((tid & 63) == 0) scratch[tid >> 6] = v;
+__device__ __forceinline__ f32x4 mma16(const bf16x8& a, const bf16x8& b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+// A X over one K step of 32: the leading product into c, the others, at most
+// 2^-7 of it, into an accumulator of their own
+__device__ __forceinline__ void mma_split(const Split& a, const Split& x, f32x4& c, f32x4& small) {
+  c = mma16(a.h, x.h, c);
+  small = mma16(a.l, x.h, small);
+  small = mma16(a.h, x.l, small);
+  small = mma16(a.m, x.m, small);
+  small = mma16(a.m, x.h, small);
+  small = mma16(a.h, x.m, small);
+}
+
+__device__ __forceinline__ bf16x8 frag_at(const uint8_t* p) { return *reinterpret_cast<const bf16x8*>(p); }
+
+// Block-wide reduction of one value per thread (every thread gets the result);
+// waves are combined in order.
+__device__ __forceinline__ float block_reduce(float v, bool is_max, float* scratch) {
+  v = is_max ? wave_max(v) : wave_sum(v);
+  if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = v;
   __syncthreads();
   float r = scratch[0];
-  for (int i = 1; i < NT / 64; ++i) r = is_max ? fmaxf(r, scratch[i]) : r + scratch[i];
-  __syncthreads();
+#pragma unroll
+  for (int i = 1; i < NW; ++i) r = is_max ? fmaxf(r, scratch[i]) : r + scratch[i];
   return r;
 }
 
-// LDS: H [F][64] | X-or-T region | logits [(P+1)*64] overlapping X/T after the tower | scratch |
-// weight staging
+// LDS: activations [SLOTS][3][Fp] bf16 + 16 bytes a slot (logits overlay them after
+// the tower) | scratch
+template <int MB, int NB>
 __global__ __launch_bounds__(NT) void az_net_f32_kernel(AzDevNet p, const float* __restrict__ planes,
-                                                        const uint8_t* __restrict__ legal, int B,
-                                                        float* __restrict__ policy,
-                                                        float* __restrict__ value, int wcap) {
-  extern __shared__ float sm[];
-  const int F = p.filters, Cin = p.in_planes, P = p.policy_planes;
-  const int b = blockIdx.x;
-  if (b >= B) return;
-  const int tid = threadIdx.x;
-  float* Hs = sm;
-  float* Xs = sm + F * 64;
-  float* Ts = sm + F * 64 + Cin * 64;
-  const int region = (Cin + F) * 64 > (P + 1) * 64 ? (Cin + F) * 64 : (P + 1) * 64;
-  float* scratch = sm + F * 64 + region;
-  float* wst = scratch + 16;
+                                                        const uint8_t* __restrict__ legal,
+                                                        float* __restrict__ policy, float* __restrict__ value,
+                                                        int scratch_off) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t sm[];
+  const int F = p.filters, Cin = p.in_planes, P = p.policy_planes, H = p.value_hidden;
+  const int M16 = (F + 15) / 16, CP = (F + 31) / 32;  // output channel blocks, input channel steps
+  const int RB = CP * 64, CS = 3 * RB + 16, RS = 9 * CS;
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kq = lane >> 4, col = lane & 7, hi4 = (lane >> 3) & 1;  // K quarter; column and half of a block's square
+  constexpr int NU = 4 / NB;                                        // waves per channel block
+  const int mb0 = w / NU * MB, nb0 = w % NU * NB;
+  const bool busy = mb0 < M16;
   const float cap = p.act_cap;
+  float* scratch = reinterpret_cast<float*>(sm + scratch_off);
 
-  for (int i = tid; i < Cin * 64; i += NT) Xs[i] = planes[(size_t)b * Cin * 64 + i];
-  __syncthreads();
-
-  const float* tw = static_cast<const float*>(p.tower_w);
-  conv3x3_f32(Xs, Cin, static_cast<const float*>(p.stem_w), p.bias, Hs, F, false, cap, wst, wcap);
-  for (int j = 0; j < p.blocks; ++j) {
-    conv3x3_f32(Hs, F, tw + (size_t)(2 * j) * F * F * 9, p.bias + (size_t)(1 + 2 * j) * F, Ts, F,
-                false, cap, wst, wcap);
-    conv3x3_f32(Ts, F, tw + (size_t)(2 * j + 1) * F * F * 9, p.bias + (size_t)(2 + 2 * j) * F, Hs,
-                F, true, cap, wst, wcap);
-  }
-
-  // heads: rows 0..P-1 policy planes, row P the value 1x1 conv; eight rows per
-  // wave pass (weights [ceil((P+1)/8)][F][8]), one square per lane
-  float* L = Xs;
-  {
-    const int sq = tid & 63, g = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const float4* hw = static_cast<const float4*>(p.head_w);
-    for (int rb = g; rb < (P + 1 + 7) / 8; rb += NT / 64) {
-      float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      const float4* w = hw + (size_t)rb * F * 2;
-      for (int f = 0; f < F; ++f) {
-        const float xv = Hs[f * 64 + sq];
-        const float4 a = w[2 * f], b = w[2 * f + 1];
-        acc[0] = fmaf(a.x, xv, acc[0]);
-        acc[1] = fmaf(a.y, xv, acc[1]);
-        acc[2] = fmaf(a.z, xv, acc[2]);
-        acc[3] = fmaf(a.w, xv, acc[3]);
-        acc[4] = fmaf(b.x, xv, acc[4]);
-        acc[5] = fmaf(b.y, xv, acc[5]);
-        acc[6] = fmaf(b.z, xv, acc[6]);
-        acc[7] = fmaf(b.w, xv, acc[7]);
-      }
+  // weights: fragment (dx, channel step, dy, channel block, part) of 1 KB each.  A
+  // wave whose second channel block is past the last one multiplies the last again
+  // and drops it.
+  Split A[3][MB];
+  auto load_a = [&](const uint8_t* g, int d) {  // g: the (dx, channel step) group
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int row = rb * 8 + j;
-        if (row <= P) L[row * 64 + sq] = acc[j] + p.head_b[row];
-      }
+    for (int m = 0; m < MB; ++m) {
+      const int mb = mb0 + m < M16 ? mb0 + m : M16 - 1;
+      const uint8_t* q = g + ((size_t)(d * M16 + mb) * 3) * 1024 + lane * 16;
+      A[d][m].h = frag_at(q);
+      A[d][m].m = frag_at(q + 1024);
+      A[d][m].l = frag_at(q + 2048);
     }
+  };
+  const size_t group = (size_t)9 * M16 * 1024;
+  const uint8_t* sw = static_cast<const uint8_t*>(p.stem_w);
+#pragma unroll
+  for (int d = 0; d < 3; ++d) load_a(sw, d);
+
+  // ---- ingest: clear the buffer (zero borders and padding channels), then the
+  // input planes as channels 0..31 (eight planes of a square per wave item)
+  float pv[8];
+  if (w < 4) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const int c = 8 * w + t;
+      const float x = planes[((size_t)b * Cin + (c < Cin ? c : 0)) * 64 + lane];
+      pv[t] = c < Cin ? x : 0.0f;
+    }
+  }
+  for (int i = tid; i < SLOTS * CS / 16; i += NT) *reinterpret_cast<i32x4*>(sm + i * 16) = i32x4{0, 0, 0, 0};
+  __syncthreads();
+  if (w < 4) {
+    uint32_t h[8], m[8], l[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) split3(pv[t], h[t], m[t], l[t]);
+    uint8_t* dst = sm + (((lane >> 3) + 1) * 9 + (lane & 7) + 1) * CS + w * 16;
+    auto put = [&](int part, const uint32_t(&v)[8]) {
+      *reinterpret_cast<uint4*>(dst + part * RB) =
+          make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
+    };
+    put(0, h);
+    put(1, m);
+    put(2, l);
   }
   __syncthreads();
 
-  const int NM = P * 64;
-  const uint8_t* lg = legal + (size_t)b * NM;
-  float* pol = policy + (size_t)b * NM;
-  float mx = -INFINITY;
-  for (int i = tid; i < NM; i += NT)
-    if (lg[i]) mx = fmaxf(mx, L[i]);
-  mx = block_reduce(mx, true, scratch);
-  float sum = 0.0f;
-  if (mx != -INFINITY)
-    for (int i = tid; i < NM; i += NT)
-      if (lg[i]) sum += expf(L[i] - mx);
-  sum = block_reduce(sum, false, scratch);
-  const float inv = sum > 0.0f ? 1.0f / sum : 0.0f;
-  for (int i = tid; i < NM; i += NT) pol[i] = lg[i] ? expf(L[i] - mx) * inv : 0.0f;
-
-  if (tid < 64) {
-    const int lane = tid;
-    const float* u = L + NM;
-    float part = 0.0f;
-    for (int k = lane; k < p.value_hidden; k += 64) {
-      const float* wr = p.fc1_w + (size_t)k * 64;
-      float g = p.fc1_b[k];
-      for (int s = 0; s < 64; ++s) {
-        const float us = p.value_conv_relu ? fmaxf(u[s], 0.0f) : u[s];
-        g = fmaf(wr[s], us, g);
+  // ---- the stem and the residual convolutions
+  const uint8_t* xb = sm + ((nb0 + 4 * hi4 + 1) * 9 + col + 1) * CS + kq * 16;  // block nb0, dx = 0
+  float res[MB][NB][4];
+  // cp channel steps; next: the following layer's first group
+  auto conv = [&](const uint8_t* wl, int cp, const uint8_t* next, const float* bias, bool residual, bool last) {
+    f32x4 acc[MB][NB], sml[MB][NB];
+    float4 bb[MB];
+    if (busy) {
+#pragma unroll
+      for (int m = 0; m < MB; ++m) {
+        bb[m] = make_float4(0.f, 0.f, 0.f, 0.f);
+        const int ch = (mb0 + m) * 16 + 4 * kq;
+        if (ch < F) bb[m] = *reinterpret_cast<const float4*>(bias + ch);  // F is a multiple of 8
+#pragma unroll
+        for (int n = 0; n < NB; ++n) acc[m][n] = sml[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
-      part = fmaf(p.fc2_w[k], fmaxf(g, 0.0f), part);
+      const uint8_t* g = wl;
+      for (int dx = 0; dx < 3; ++dx) {
+        for (int cs = 0; cs < cp; ++cs) {
+          g = dx == 2 && cs + 1 == cp ? next : g + group;
+          Split X[NB + 2];  // blocks nb0 - 1 .. nb0 + NB
+          const uint8_t* q = xb + (dx - 1) * CS + cs * 64 - RS;
+#pragma unroll
+          for (int x = 0; x < NB + 2; ++x) {
+            X[x].h = frag_at(q + x * RS);
+            X[x].m = frag_at(q + x * RS + RB);
+            X[x].l = frag_at(q + x * RS + 2 * RB);
+          }
+#pragma unroll
+          for (int d = 0; d < 3; ++d) {
+#pragma unroll
+            for (int m = 0; m < MB; ++m)
+#pragma unroll
+              for (int n = 0; n < NB; ++n) mma_split(A[d][m], X[n + d], acc[m][n], sml[m][n]);
+            load_a(g, d);  // the next group's, two vertical taps ahead
+          }
+        }
+      }
     }
-    for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o);
-    if (lane == 0) value[b] = tanhf(part + p.fc2_b);
+    __syncthreads();  // every wave has read the buffer
+    if (busy) {
+#pragma unroll
+      for (int m = 0; m < MB; ++m) {
+        const float bv[4] = {bb[m].x, bb[m].y, bb[m].z, bb[m].w};
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+          uint32_t h[4], md[4], l[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            float y = acc[m][n][r] + sml[m][n][r] + bv[r];
+            if (residual) y += res[m][n][r];
+            y = act_fn(y, cap);
+            if (residual || last) res[m][n][r] = y;
+            split3(y, h[r], md[r], l[r]);
+          }
+          if (mb0 + m < M16) {
+            uint8_t* dst = sm + ((nb0 + n + 4 * hi4 + 1) * 9 + col + 1) * CS + (mb0 + m) * 32 + kq * 8;
+            *reinterpret_cast<uint2*>(dst) = make_uint2(h[0] | h[1] << 16, h[2] | h[3] << 16);
+            *reinterpret_cast<uint2*>(dst + RB) = make_uint2(md[0] | md[1] << 16, md[2] | md[3] << 16);
+            *reinterpret_cast<uint2*>(dst + 2 * RB) = make_uint2(l[0] | l[1] << 16, l[2] | l[3] << 16);
+          }
+        }
+      }
+    }
+    __syncthreads();
+  };
+  const uint8_t* tw = static_cast<const uint8_t*>(p.tower_w);
+  const size_t layer = (size_t)3 * CP * group;
+  conv(sw, 1, tw, p.bias, false, true);
+  if (M16 == 1 && tid < 64 * 3) {
+    // one channel block: the stem input's channels 16..31 give way to zeros
+    uint8_t* dst = sm + (((tid & 63) / 8 + 1) * 9 + (tid & 7) + 1) * CS + tid / 64 * RB + 32;
+    *reinterpret_cast<i32x4*>(dst) = i32x4{0, 0, 0, 0};
+    *reinterpret_cast<i32x4*>(dst + 16) = i32x4{0, 0, 0, 0};
   }
+  if (M16 == 1) __syncthreads();
+  for (int n = 0; n < 2 * p.blocks; ++n) {
+    const uint8_t* wl = tw + n * layer;
+    // past the last layer the last one's start is re-read (never used)
+    conv(wl, CP, n + 1 < 2 * p.blocks ? wl + layer : wl, p.bias + (size_t)(n + 1) * F, n & 1, false);
+  }
+
+  // ---- heads: rows 0..P-1 policy planes, row P the value 1x1 conv.  Wave w takes
+  // square block w % 4 and row blocks w / 4, w / 4 + 2, w / 4 + 4.  The legal mask
+  // and fc1 (hidden unit tid) are in flight meanwhile.
+  const int NM = P * 64;
+  constexpr int UN = (CELLS / 4 + NT - 1) / NT;  // 4-cell units of a thread
+  const uint8_t* lg = legal + (size_t)b * NM;
+  uint32_t mk[UN];
+#pragma unroll
+  for (int i = 0; i < UN; ++i) {
+    const int c = 4 * (tid + i * NT);
+    const uint32_t x = *reinterpret_cast<const uint32_t*>(lg + (c < NM ? c : 0));
+    mk[i] = c < NM ? x : 0u;
+  }
+  const bool unit = tid < H;
+  float4 f1[16];
+#pragma unroll
+  for (int s = 0; s < 16; ++s) f1[s] = reinterpret_cast<const float4*>(p.fc1_t)[(size_t)s * H + (unit ? tid : 0)];
+  const float f1b = p.fc1_b[unit ? tid : 0], f2 = unit ? p.fc2_w[tid] : 0.0f;
+  {
+    const int RBK = (P + 16) / 16, nb = w & 3, rb0 = w >> 2;
+    const uint8_t* hw = static_cast<const uint8_t*>(p.head_w) + lane * 16;
+    const uint8_t* q = sm + ((nb + 4 * hi4 + 1) * 9 + col + 1) * CS + kq * 16;
+    f32x4 acc[3], sml[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) acc[i] = sml[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int cs = 0; cs < CP; ++cs) {
+      const Split x = {frag_at(q + cs * 64), frag_at(q + cs * 64 + RB), frag_at(q + cs * 64 + 2 * RB)};
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        const int rb = rb0 + 2 * i < RBK ? rb0 + 2 * i : RBK - 1;
+        const uint8_t* a = hw + (size_t)(cs * RBK + rb) * 3 * 1024;
+        mma_split(Split{frag_at(a), frag_at(a + 1024), frag_at(a + 2048)}, x, acc[i], sml[i]);
+      }
+    }
+    __syncthreads();
+    float* L = reinterpret_cast<float*>(sm);
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = (rb0 + 2 * i) * 16 + 4 * kq + r;
+        if (row <= P) L[row * 64 + (nb + 4 * hi4) * 8 + col] = acc[i][r] + sml[i][r] + p.head_b[row];
+      }
+  }
+  __syncthreads();
+
+  // ---- legal-move softmax and value head
+  const float* L = reinterpret_cast<const float*>(sm);
+  float e[UN][4], mx = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < UN; ++i) {
+    const int c = 4 * (tid + i * NT);
+    const float4 z = c < NM ? *reinterpret_cast<const float4*>(L + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+    const float zz[4] = {z.x, z.y, z.z, z.w};
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      e[i][t] = (mk[i] >> (8 * t)) & 0xffu ? zz[t] : -INFINITY;
+      mx = fmaxf(mx, e[i][t]);
+    }
+  }
+  float g = f1b;
+  const float* u = L + NM;
+#pragma unroll
+  for (int s = 0; s < 16; ++s) {
+    float4 us = *reinterpret_cast<const float4*>(u + 4 * s);
+    if (p.value_conv_relu) us = make_float4(fmaxf(us.x, 0.f), fmaxf(us.y, 0.f), fmaxf(us.z, 0.f), fmaxf(us.w, 0.f));
+    g = fmaf(f1[s].x, us.x, g);
+    g = fmaf(f1[s].y, us.y, g);
+    g = fmaf(f1[s].z, us.z, g);
+    g = fmaf(f1[s].w, us.w, g);
+  }
+  mx = block_reduce(mx, true, scratch);
+  const float msub = mx == -INFINITY ? 0.0f : mx;
+  float sum = 0.0f;
+#pragma unroll
+  for (int i = 0; i < UN; ++i)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      e[i][t] = e[i][t] == -INFINITY ? 0.0f : expf(e[i][t] - msub);
+      sum += e[i][t];
+    }
+  sum = block_reduce(sum, false, scratch + NW);
+  const float part = block_reduce(f2 * fmaxf(g, 0.0f), false, scratch + 2 * NW);
+  const float inv = sum > 0.0f ? 1.0f / sum : 0.0f;
+  float* pol = policy + (size_t)b * NM;
+#pragma unroll
+  for (int i = 0; i < UN; ++i) {
+    const int c = 4 * (tid + i * NT);
+    if (c < NM) *reinterpret_cast<float4*>(pol + c) = make_float4(e[i][0] * inv, e[i][1] * inv, e[i][2] * inv, e[i][3] * inv);
+  }
+  if (tid == 0) value[b] = tanhf(part + p.fc2_b);
+}
+
+template <int MB, int NB>
+hipError_t launch(const AzDevNet& n, const float* planes, const uint8_t* legal, int B, float* policy, float* value,
+                  hipStream_t s) {
+  const int slot = 3 * 64 * ((n.filters + 31) / 32) + 16;
+  const int act = SLOTS * slot, logits = (n.policy_planes + 1) * 64 * 4;
+  const int scratch_off = act > logits ? act : logits;  // multiples of 16
+  const int lds = scratch_off + 3 * NW * 4;  // 144.3 KB at 256 filters
+  if (lds > 64 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&az_net_f32_kernel<MB, NB>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL((az_net_f32_kernel<MB, NB>), dim3(B), dim3(NT), lds, s, n, planes, legal, policy, value,
+                     scratch_off);
+  return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t az_launch_f32(const AzDevNet& n, const float* planes, const uint8_t* legal, int B,
                          float* policy, float* value, hipStream_t s) {
-  const int F = n.filters, Cin = n.in_planes, P = n.policy_planes;
-  const int region = (Cin + F) * 64 > (P + 1) * 64 ? (Cin + F) * 64 : (P + 1) * 64;
-  const int base = F * 64 + region + 16;
-  const int wcap = LDS_FLOATS - base < WSTAGE_FLOATS ? (LDS_FLOATS - base > 0 ? LDS_FLOATS - base : 0) : WSTAGE_FLOATS;
-  const size_t lds = ((size_t)base + wcap) * sizeof(float);
   (void)hipGetLastError();
-  if (lds > 64 * 1024) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&az_net_f32_kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(az_net_f32_kernel, dim3(B), dim3(NT), lds, s, n, planes, legal, B, policy, value, wcap);
-  return hipGetLastError();
+  const int M16 = (n.filters + 15) / 16;  // 16-channel blocks: eight waves cover the layer's blocks once
+  if (M16 > 8) return launch<2, 4>(n, planes, legal, B, policy, value, s);
+  if (M16 > 4) return launch<1, 4>(n, planes, legal, B, policy, value, s);
+  if (M16 > 2) return launch<1, 2>(n, planes, legal, B, policy, value, s);
+  return launch<1, 1>(n, planes, legal, B, policy, value, s);
 }

@@ -281,6 +281,43 @@ void pack_conv(const float* W, const float* wscale, int F, int Cin, int Cp, Kind
   }
 }
 
+// fp32 kernel: A fragments of a matrix of `rows` output channels and `chans` input
+// channels (padded with zeros to 16 rows and 32 channels) for each of `taps`
+// matrices of a channel step: fragment (channel step, tap, row block, part), lane
+// l holds part (bf16 h, m or l of w = h + m + l) of w(row 16 mb + l%16, channel
+// 32 cs + 8 (l/16) + t, tap), t = 0..7.
+template <class W>
+void pack_split(int rows, int chans, int steps, W w, int taps, std::vector<uint8_t>& out) {
+  const int M16 = (rows + 15) / 16;
+  const size_t base = out.size();
+  out.resize(base + (size_t)steps * taps * M16 * 3 * 1024);
+  uint8_t* o = out.data() + base;
+  for (int cs = 0; cs < steps; ++cs)
+    for (int tap = 0; tap < taps; ++tap)
+      for (int mb = 0; mb < M16; ++mb, o += 3 * 1024)
+        for (int l = 0; l < 64; ++l)
+          for (int t = 0; t < 8; ++t) {
+            const int row = mb * 16 + l % 16, c = cs * 32 + 8 * (l / 16) + t;
+            float x = row < rows && c < chans ? w(row, c, tap) : 0.0f;
+            for (int part = 0; part < 3; ++part) {
+              const uint16_t h = bf16_rne(x);
+              const uint32_t u = (uint32_t)h << 16;
+              float f;
+              memcpy(&f, &u, 4);
+              memcpy(o + part * 1024 + l * 16 + 2 * t, &h, 2);
+              x = isfinite(f) ? x - f : 0.0f;
+            }
+          }
+}
+
+// A 3x3 conv W[F][C][3][3] for the fp32 kernel, groups ordered (dx, channel step),
+// the three dy of a group in order.
+void pack_conv_f32(const float* W, int F, int C, std::vector<uint8_t>& out) {
+  for (int dx = 0; dx < 3; ++dx)
+    pack_split(F, C, (C + 31) / 32, [&](int row, int c, int dy) { return W[((size_t)row * C + c) * 9 + 3 * dy + dx]; }, 3,
+               out);
+}
+
 void pack_head(const BlobView& v, int F, int P, std::vector<uint8_t>& out) {
   const int S = F / 16;
   const size_t base = out.size();
@@ -540,30 +577,13 @@ int az_net_load(const az_layer_spec* spec_in, const float* weights, size_t n_wei
         for (int c = 0; c < 64; ++c) fc1t[((size_t)(c / 4) * H + k) * 4 + (c % 4)] = v.fc1_w[(size_t)k * 64 + c];
     }
     if (dtype == AZ_F32) {
-      // fp32 kernel: convs as [F/8][C][9][8] and heads as [ceil((P+1)/8)][F][8], so
-      // that the eight output channels (rows) a thread accumulates at one (input
-      // channel, tap) are one contiguous 32-byte load
-      auto pack8 = [](const float* W, int Fo, int C, std::vector<uint8_t>& out) {
-        const size_t base = out.size();
-        out.resize(base + (size_t)Fo * C * 9 * 4);
-        float* o = reinterpret_cast<float*>(out.data() + base);
-        for (int fb = 0; fb < Fo / 8; ++fb)
-          for (int c = 0; c < C; ++c)
-            for (int t = 0; t < 9; ++t)
-              for (int j = 0; j < 8; ++j)
-                o[(((size_t)fb * C + c) * 9 + t) * 8 + j] = W[((size_t)(fb * 8 + j) * C + c) * 9 + t];
-      };
-      pack8(v.stem_w, F, Cin, stem);
-      for (int n = 0; n < 2 * NB; ++n) pack8(v.w[n], F, F, tower);
-      const int RB8 = (P + 1 + 7) / 8;
-      head.assign((size_t)RB8 * F * 8 * 4, 0);
-      float* h = reinterpret_cast<float*>(head.data());
-      for (int rb = 0; rb < RB8; ++rb)
-        for (int f = 0; f < F; ++f)
-          for (int j = 0; j < 8; ++j) {
-            const int row = rb * 8 + j;
-            h[((size_t)rb * F + f) * 8 + j] = row < P ? v.pol_w[(size_t)row * F + f] : row == P ? v.val_w[f] : 0.0f;
-          }
+      pack_conv_f32(v.stem_w, F, Cin, stem);
+      for (int n = 0; n < 2 * NB; ++n) pack_conv_f32(v.w[n], F, F, tower);
+      // heads: P policy rows, then the value 1x1 conv's
+      std::vector<float> hw((size_t)(P + 1) * F);
+      memcpy(hw.data(), v.pol_w, (size_t)P * F * sizeof(float));
+      memcpy(hw.data() + (size_t)P * F, v.val_w, (size_t)F * sizeof(float));
+      pack_split(P + 1, F, (F + 31) / 32, [&](int row, int k, int) { return hw[(size_t)row * F + k]; }, 1, head);
     } else {
       pack_conv(v.stem_w, nullptr, F, Cin, dep ? AZ_DEP_MAX_IN_PLANES : 32, K_BF16, !dep, stem);
       const Kind kind = dtype == AZ_BF16 ? K_BF16 : dtype == AZ_INT8 ? K_I8 : K_F8;

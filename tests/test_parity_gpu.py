@@ -478,6 +478,24 @@ def test_f32_wide_networks(filters, blocks):
     H.compare_f32(Pg, Vg, Pr, Vr)
 
 
+@pytest.mark.parametrize("filters", [8, 16, 24, 32, 40, 72, 136, 200])
+def test_f32_filter_counts(filters):
+    # channel counts at and off the 16-row and 32-channel blocks of the fp32 kernel
+    # and on both sides of each wave tile's range, with 12 planes, 95 and 1 policy
+    # planes; the fp32 gate against float64
+    for in_planes, planes_out, hidden in ((12, 95, 512), (32, 1, 30)):
+        shape = azgen.NetShape(in_planes=in_planes, blocks=2, filters=filters, policy_planes=planes_out,
+                               value_hidden=hidden, value_conv_relu=1)
+        blob = azgen.make_weights(shape, 930 + filters, alpha_fold=True, bf16=False)
+        _scale_fc2(shape, blob, 1.0 / 8)
+        planes, legal = _shape_inputs(shape, 5, 16)
+        _print(f"case f32 F={filters} C={in_planes} P={planes_out}")
+        Pg, Vg = H.gpu_eval(shape, blob, "f32", planes, legal)
+        H.assert_policy_structure(Pg, legal)
+        Pr, Vr = O.forward(shape, blob, planes, legal)
+        H.compare_f32(Pg, Vg, Pr, Vr)
+
+
 # --------------------------------------------------------------------------- #
 # Deployment validation (per-row comparison kernel and the validate() gate)
 # --------------------------------------------------------------------------- #
