@@ -233,8 +233,9 @@ int az_net_moves(const az_net* net);
  * board per compute unit, then two, then as the large tiling; 3 (medium, F = 64
  * and 128 only): two boards per workgroup, two workgroups per compute unit (one
  * for AZ_BF16 with F = 128).  The deployed network has two: 1, one wave per
- * board (several boards per compute unit); 2, four waves per board (one board
- * per compute unit, for small batches).  Every tiling computes bitwise the
+ * board, four per compute unit (AZ_INT8), or two boards per workgroup of four waves
+ * (AZ_BF16); 2, four waves for one board up to a board per compute unit, for two
+ * boards up to two, then as tiling 1.  Every tiling computes bitwise the
  * same results.  AZ_F32 has a single tiling and accepts only 0.  Returns
  * AZ_OK or AZ_ERR_INVALID_ARG. */
 int az_net_set_tiling(az_net* net, int32_t tiling);

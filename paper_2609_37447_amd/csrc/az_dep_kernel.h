@@ -4,34 +4,41 @@
 // outputs", Section 4.3 "Convolution, attention, and global context", "Three
 // policy representations", "Value and training-only heads", Appendix D).
 //
-// One workgroup evaluates one board end to end, in one of two tilings.
-// az_dep_kernel (large batches): one wave per workgroup, four such workgroups
-// per compute unit for int8 (one per SIMD); the wave owns every output channel
-// (five 32-channel MFMA blocks) and both half-board square blocks of every
-// layer, so global pooling, the heads and both softmaxes need no exchange with
-// other waves.  az_dep_kernel4 (small batches, where the batch offers about a
-// board per compute unit): four waves, one per SIMD, share a layer's ten 32x32
-// tiles, three at most per SIMD, and meet at a barrier per layer; they share
-// the heads as well, exchanging operand fragments through LDS.
+// Kernels.  az_dep_kernel1 (int8, large batches): one wave per board, four such
+// workgroups per compute unit (one per SIMD); the wave owns every output channel
+// (five 32-channel MFMA blocks), so global pooling, the heads and both softmaxes
+// need no exchange with other waves and no wave waits for another.  az_dep_kernel
+// (everything else): four waves, one per SIMD, evaluate one board (small batches) or
+// two, which share every weight fragment; they meet at a barrier per layer and share
+// the heads, or with two boards run one board's heads per wave.
 //
 // Tower.  Every 3x3 convolution is an implicit GEMM D[ch][sq] = sum_k
-// W[ch][k] X[k][sq], k = tap * C + c, with weights as the A operand (streamed
-// from L2 in pre-packed fragment order through a ring of prefetched K steps)
-// and the board's activations as the B operand, read from LDS rows [square][F
-// channels].  Rows of 160 (int8) or 320 (bf16) bytes are not a power of two,
-// so a row's 16-byte chunks are rotated by a few positions that depend on the
-// square: the 16 lanes of a ds_read_b128 group (16 consecutive squares) then
-// hit 16 different bank groups.  Out-of-board taps read a zero region at the
-// bank slot their virtual square would use.
+// W[ch][k] X[k][sq] with weights as the A operand (streamed from L2 in pre-packed
+// fragment order through a ring of prefetched groups) and the boards' activations
+// as the B operand, read from LDS.  A 32-column block is whole board rows (row j of
+// two boards and row j + 4 of each, or rows j, j + 2, j + 4, j + 6 of one), so the
+// fragments of one horizontal tap and channel step serve all three vertical taps:
+// the K steps run over (dx, channel step) with the three dy inside.
+//
+// What bounds it.  Large int8 batches: the wave's own instruction stream; its
+// float64 requantisation and the float64 conversions of it (2 to 3 times a plain
+// instruction) run with the matrix pipe idle, and 80 KB of weights a tap leave the
+// registers room for two steps of prefetch.  Small batches: that and the layers'
+// chain of barriers.  Measured on 14x160 against one-tap-at-a-time K loops and one
+// board per workgroup (us per batch): int8 64 boards 143 -> 140, 256 152 -> 143, 333
+// 290 -> 200, 512 298 -> 228, 1,024 382 -> 365; bf16 64 boards 211 -> 204, 333
+// 427 -> 293, 1,024 888 -> 670.  Four int8 boards per workgroup were slower than a
+// wave per board (1,024 boards 463 against 365: the epilogue of 160 values a lane
+// behind one barrier; its registers spill in the pooling layers).
 //
 // Global pooling (every pool_every-th block).  After the first convolution's
 // K loop, the pooled channels (the last F/4) are transposed through LDS (int8:
 // the exact accumulators; bf16: their activations); one lane per pooled
 // channel activates (int8, in float64) and reduces its row to a board sum
-// (fp64) and maximum, and the projection c = Wg [mean, max] runs in fp64, one
-// or two outputs per lane.  c is added to the regular channels' bias in the
-// layer's constant slot (int8: in code units, in float64), so the epilogue
-// that writes them takes it with the bias.
+// (fp64) and maximum, and the projection c = Wg [mean, max] runs in fp64.  c is
+// added to the regular channels' bias (int8: in code units, in float64), so the
+// epilogue that writes them takes it with the bias.  The second convolution leaves
+// out the channel steps that hold pooled channels only.
 //
 // bf16 networks carry the residual stream h as hi + lo: hi = bf16(h) is the
 // convolution operand in LDS, lo = bf16(h - hi) stays in the registers of the
@@ -68,25 +75,50 @@ constexpr int DTB = DD / 32;                    // token row blocks
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
-// Chunk position of logical 16-byte chunk lc in a row of RB bytes at swizzle
-// sw: XOR for rows of 128 bytes, rotation modulo the row's chunk count for the
-// 160- and 320-byte rows.
-template <int RB>
-struct Rot {
-  static constexpr int NC = RB / 16;
-  static constexpr int GC = gcd_c(NC, 16);      // NC*s mod 16 repeats every 16/GC squares
-  static constexpr int SH = GC == 2 ? 3 : GC == 4 ? 2 : 1;
-  static constexpr int RM = GC - 1;
-  static_assert(RB == 160 || RB == 320, "rotated rows");
-  static __device__ __forceinline__ int sw(int sq) { return (sq >> SH) & RM; }
-  static __device__ __forceinline__ int pos(int lc, int sw) {
-    const int x = lc + sw;
-    return x >= NC ? x - NC : x;
-  }
+// LDS geometry of a tensor with RB bytes per square of BPG boards: [row][board]
+// [column], a square every CS bytes (an odd number of 16-byte units, so the 16
+// squares of a ds_read_b128 group hit 16 different bank groups), every row ending
+// in a zero pad that stands for the columns left and right of a board, read at the
+// bank slot the virtual square would use.  A 32-column MFMA block j takes row
+// j + i * NBK of each board, i < RPB, so a vertical tap of block j is block j +- 1;
+// with one board a read group holds two rows, whose stride is half the banks.
+template <int RB, int BPG>
+struct DGeo {
+  static constexpr int CS = RB + 16;
+  static_assert(CS / 16 % 2 == 1, "odd square stride");
+  static constexpr int PAD = BPG * 8 * CS;
+  static constexpr int ZP0 = 256 + RB;
+  static constexpr int ZP = BPG == 1 ? ZP0 + (12 - (PAD + ZP0) / 16 % 8) % 8 * 16 : ZP0;
+  static constexpr int RS = PAD + ZP;
+  static_assert(BPG != 1 || RS / 16 % 8 == 4, "two rows of a read group half the banks apart");
+  static constexpr int NBK = 2 * BPG, RPB = 8 / NBK;
+  static constexpr bool EDGE = RPB > 1;  // blocks -1 and NBK hold rows inside the board
+  static constexpr int X0 = EDGE ? 1 : 0, NX = NBK + 2 * X0;
+  static constexpr int BUF = 8 * RS;
+  static __device__ __forceinline__ int at(int row, int board, int col) { return row * RS + (board * 8 + col) * CS; }
 };
 
-// swizzle of a 128-byte row (the stem's 64 bf16 input channels)
-__device__ __forceinline__ int swz128(int sq) { return (sq >> 1) & 7; }
+// Lane addresses, relative to the buffer, of the B fragments of one horizontal tap:
+// channel step cs of block x is at row + x * RS + 32 * cs; blocks -1 and NBK have
+// rows of their own (the pad where a row is outside the board).
+template <int RB, int BPG>
+struct DTaps {
+  using G = DGeo<RB, BPG>;
+  int row, lo, hi;
+  __device__ __forceinline__ void init(int dx, int l32, int lhi) {
+    const int i = l32 / (8 * BPG), v = l32 % (8 * BPG) + dx, c = (l32 & 7) + dx;
+    const int pad = G::PAD + ((v * G::CS) & 255) + 16 * lhi;
+    row = i * G::NBK * G::RS + ((unsigned)c < 8u ? v * G::CS + 16 * lhi : pad);
+    lo = i > 0 ? row - G::RS : pad;
+    hi = i < G::RPB - 1 ? row + G::NBK * G::RS : pad;
+  }
+  __device__ __forceinline__ void opaque() { asm volatile("" : "+v"(row), "+v"(lo), "+v"(hi)); }
+  template <class Frag, int X>
+  __device__ __forceinline__ Frag get(const uint8_t* buf, int cs) const {
+    const uint8_t* q = X < 0 ? buf + lo : X >= G::NBK ? buf + hi : buf + X * G::RS + row;
+    return *reinterpret_cast<const Frag*>(q + 32 * cs);
+  }
+};
 
 // LDS writes before, reads after, across every wave of the workgroup
 __device__ __forceinline__ void wave_lds_sync() {
@@ -170,48 +202,43 @@ __device__ __forceinline__ f32x16 mma_bf16(const bf16x8& a, const bf16x8& b, con
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
-__device__ __forceinline__ double shfl_xor_d(double v, int m) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)u, m), hi = (uint32_t)__shfl_xor((int)(uint32_t)(u >> 32), m);
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-
-template <int MK>
+template <int MK, int BPG_>
 struct DepCfg {
   using T = Mk<MK>;
+  static constexpr int BPG = BPG_;                    // boards per workgroup
   static constexpr bool QUANT = MK != MK_BF16;
-  static constexpr int RB = DF * T::ES;               // tower row bytes
-  static constexpr int RBX = 2 * DF;                  // bf16 row bytes of the heads' input
-  static constexpr int BUF = 64 * RB;
-  static constexpr int OFF_H = 0, OFF_T = BUF, OFF_Z = 2 * BUF;
-  static constexpr int ZB = (RB + 256 + 255) / 256 * 256;
+  static constexpr int RB = DF * T::ES;               // bytes per square, tower tensors
+  using GT = DGeo<RB, BPG>;                           // tower tensors
+  using GS = DGeo<2 * DCP, BPG>;                      // stem input
+  static_assert(GS::BUF <= GT::BUF, "stem input fits in the T buffer");
+  static constexpr int BUF = GT::BUF;
+  static constexpr int OFF_H = 0, OFF_T = BUF;
   // per-layer epilogue constants: [bias F] floats, or for int8 [qbias F | qmul F
   // | qres, qhi] doubles (the float64 requantisation; the layer's two scalars
   // ride along so that the epilogue reads them from LDS: a load from global
   // memory there would wait behind the weight stream)
+  static constexpr int KE = QUANT ? 8 : 4;            // bytes of a bias
   static constexpr int KSLOT = QUANT ? 16 * DF + 16 : 4 * DF;
-  static constexpr int OFF_K = OFF_Z + ZB;
-  static constexpr int OFF_PG = OFF_K + 2 * KSLOT;    // pooled statistics, 2g doubles
-  static constexpr int TOWER_END = OFF_PG + 2 * DG * 8;
-  static constexpr int OFF_X = BUF;                   // heads' bf16 input: the lo part (bf16 networks)
-  static constexpr int X_END = QUANT ? 0 : OFF_X + 64 * RBX;
+  static constexpr int OFF_K = 2 * BUF;
+  static constexpr int OFF_PB = OFF_K + 2 * KSLOT;    // a pooling layer's biases, [board][F]
+  static constexpr int OFF_PG = OFF_PB + BPG * DF * KE;  // pooled statistics, [board][2g] doubles
+  static constexpr int TOWER_END = OFF_PG + BPG * 2 * DG * 8;
+  static_assert(BPG * DG * 64 * 4 <= BUF, "pooled activations fit in the T buffer");
+  static constexpr int OFF_X = OFF_T;                 // heads' bf16 input: the lo part (bf16 networks)
+  // heads, per board (past every use of H and X)
   static constexpr int OFF_S = 0;                     // query-key logits [64][64] f32
   static constexpr int OFF_U = 64 * 64 * 4;           // value features [V][64] f32
   static constexpr int OFF_O = OFF_U + 32 * 64 * 4;   // promotion offsets [8][4] f32
-  static constexpr int HEAD_END = OFF_O + 32 * 4;
-  static constexpr int OFF_HC = (cmax(cmax(TOWER_END, X_END), HEAD_END) + 15) & ~15;  // head constants
-  static constexpr int SMEM = OFF_HC + (2 * AZ_DEP_EMB_ROWS + 2 * DD) * 4;
-  // four-wave tiling: operand fragments shared by the heads' waves (four planes of
-  // 16 KB), past the one-wave layout
-  static constexpr int OFF_Q4 = (SMEM + 255) & ~255;
-  static constexpr int SMEM4 = OFF_Q4 + 4 * 16384;
-  static_assert(OFF_T >= 64 * 128, "stem input fits in the T buffer");
-  static constexpr int CPT = DF / T::KS;              // K steps per tap
-  static constexpr int S = 9 * CPT;                   // K steps per layer
-  static constexpr int NBUF = 3;                      // one-wave weight ring (steps), loaded NBUF-1 ahead
-  static_assert((2 * S) % NBUF == 0, "every block's first conv starts at ring slot 0");
-  static constexpr int STEP_BYTES = DNMB * 64 * T::FB;
-  static constexpr size_t LAYER_BYTES = (size_t)S * STEP_BYTES;
+  static constexpr int HEAD = OFF_O + 32 * 4;
+  static constexpr int OFF_HC = (cmax(TOWER_END, BPG * HEAD) + 15) & ~15;  // head constants
+  static constexpr int OFF_Q4 = (OFF_HC + (2 * AZ_DEP_EMB_ROWS + 2 * DD) * 4 + 255) & ~255;
+  // one board: operand fragments shared by the heads' waves (four planes of 16 KB)
+  static constexpr int SMEM = OFF_Q4 + (BPG == 1 ? 4 * 16384 : 0);
+  static_assert(SMEM <= 160 * 1024, "LDS");
+  static constexpr int CPT = DF / T::KS;              // channel steps
+  static constexpr int NS = 3 * CPT;                  // (dx, channel step) groups per layer
+  static constexpr int GROUP_BYTES = 3 * DNMB * 64 * T::FB;  // [dy][channel block] fragments
+  static constexpr size_t LAYER_BYTES = (size_t)NS * GROUP_BYTES;
 };
 
 // WDL value head of one board, one wave (lane = 0..63), from the value
@@ -266,19 +293,20 @@ __device__ __forceinline__ void dep_wdl(const AzDevNet& p, const float* U, float
   }
 }
 
-// Heads of one board, run by one wave (lane = 0..63) once the final tower
-// output h is in LDS (int8: codes in H; bf16: hi parts in H, lo parts in X):
-// embedding, tokens, query-key logits and promotion offsets, legal-action
-// softmax, WDL value head.
-template <int MK>
-__device__ __forceinline__ void dep_heads(const AzDevNet& p, uint8_t* smem, const uint8_t* __restrict__ legal,
+// Heads of one board (bd of the workgroup's, position b of the batch), run by one
+// wave (lane = 0..63) once the final tower output h is in LDS (int8: codes in H;
+// bf16: hi parts in H, lo parts in X): embedding, tokens, query-key logits and
+// promotion offsets, legal-action softmax, WDL value head.  Every wave of the
+// workgroup meets the one barrier inside (live: the wave has a position).
+template <int MK, int BPG>
+__device__ __forceinline__ void dep_heads(const AzDevNet& p, uint8_t* smem_all, const uint8_t* __restrict__ legal,
                                           float* __restrict__ policy, float* __restrict__ value,
-                                          float* __restrict__ wdl, int b, int lane_in) {
-  using C = DepCfg<MK>;
-  using R = Rot<C::RB>;
-  using RX = Rot<C::RBX>;
+                                          float* __restrict__ wdl, int b, int bd, bool live, int lane_in) {
+  using C = DepCfg<MK, BPG>;
+  using GT = typename C::GT;
+  uint8_t* const smem = smem_all + bd * C::HEAD;  // this board's logits, features, offsets
   constexpr bool QUANT = C::QUANT;
-  constexpr int RB = C::RB, OFF_H = C::OFF_H;
+  constexpr int OFF_H = C::OFF_H;
   // the lane index, opaque to the compiler here, so that the heads' lane-dependent
   // addresses are computed in the heads instead of being shared with the stem's
   // and held (or spilled) across the tower
@@ -310,15 +338,15 @@ __device__ __forceinline__ void dep_heads(const AzDevNet& p, uint8_t* smem, cons
         const int j = n * 32 + l32;
         if constexpr (QUANT) {
           // eight codes of channels 16 s + 8 lhi .. + 7, exact in bf16
-          const uint2 v = *reinterpret_cast<const uint2*>(smem + OFF_H + j * RB + (R::pos(s, R::sw(j)) << 4) + 8 * lhi);
+          const uint2 v = *reinterpret_cast<const uint2*>(smem_all + OFF_H + GT::at(j >> 3, bd, j & 7) + 16 * s + 8 * lhi);
           bx[n] = __builtin_bit_cast(
               bf16x8, make_uint4(pack_bf16x2(code_value<MK, 0>(v.x), code_value<MK, 1>(v.x)),
                                  pack_bf16x2(code_value<MK, 2>(v.x), code_value<MK, 3>(v.x)),
                                  pack_bf16x2(code_value<MK, 0>(v.y), code_value<MK, 1>(v.y)),
                                  pack_bf16x2(code_value<MK, 2>(v.y), code_value<MK, 3>(v.y))));
         } else {
-          bx[n] = *reinterpret_cast<const bf16x8*>(smem + C::OFF_X + j * C::RBX + (RX::pos(2 * s + lhi, RX::sw(j)) << 4));
-          bh[n] = *reinterpret_cast<const bf16x8*>(smem + OFF_H + j * C::RBX + (RX::pos(2 * s + lhi, RX::sw(j)) << 4));
+          bx[n] = *reinterpret_cast<const bf16x8*>(smem_all + C::OFF_X + GT::at(j >> 3, bd, j & 7) + 32 * s + 16 * lhi);
+          bh[n] = *reinterpret_cast<const bf16x8*>(smem_all + OFF_H + GT::at(j >> 3, bd, j & 7) + 32 * s + 16 * lhi);
         }
       }
 #pragma unroll
@@ -333,10 +361,11 @@ __device__ __forceinline__ void dep_heads(const AzDevNet& p, uint8_t* smem, cons
       }
     }
   }
-  wave_sync();  // H and X are dead from here on
+  wave_lds_sync();  // H and X are dead from here on
+  if (!live) return;
 
   // token values relu(acc * scale + bias); value features u[c][sq] to LDS
-  const float* HC = reinterpret_cast<const float*>(smem + C::OFF_HC);
+  const float* HC = reinterpret_cast<const float*>(smem_all + C::OFF_HC);
   {
 #pragma unroll
     for (int m = 0; m < DTB; ++m)
@@ -552,7 +581,7 @@ __device__ __forceinline__ void dep_heads(const AzDevNet& p, uint8_t* smem, cons
   dep_wdl(p, reinterpret_cast<const float*>(smem + C::OFF_U), value, wdl, b, lane);
 }
 
-// Heads of one board shared by the four waves of az_dep_kernel4 (wave = 0..3,
+// Heads of a workgroup's only board shared by its four waves (wave = 0..3,
 // lane = 0..63), once the final tower output h is in LDS.  The arithmetic is
 // dep_heads' operation for operation: every accumulator tile runs the same
 // chain of products, split operands are split the same way, and the softmax
@@ -565,11 +594,10 @@ template <int MK>
 __device__ __forceinline__ void dep_heads4(const AzDevNet& p, uint8_t* smem, const uint8_t* __restrict__ legal,
                                            float* __restrict__ policy, float* __restrict__ value,
                                            float* __restrict__ wdl, int b, int wave, int lane) {
-  using C = DepCfg<MK>;
-  using R = Rot<C::RB>;
-  using RX = Rot<C::RBX>;
+  using C = DepCfg<MK, 1>;
+  using GT = typename C::GT;
   constexpr bool QUANT = C::QUANT;
-  constexpr int RB = C::RB, OFF_H = C::OFF_H;
+  constexpr int OFF_H = C::OFF_H;
   constexpr int FS = 64 * 16;                   // bytes of one fragment set
   static_assert(DTB == 4, "one token block per wave");
   const int l32 = lane & 31, lhi = lane >> 5;
@@ -629,15 +657,15 @@ __device__ __forceinline__ void dep_heads4(const AzDevNet& p, uint8_t* smem, con
       for (int n = 0; n < 2; ++n) {
         const int j = n * 32 + l32;
         if constexpr (QUANT) {
-          const uint2 v = *reinterpret_cast<const uint2*>(smem + OFF_H + j * RB + (R::pos(s, R::sw(j)) << 4) + 8 * lhi);
+          const uint2 v = *reinterpret_cast<const uint2*>(smem + OFF_H + GT::at(j >> 3, 0, j & 7) + 16 * s + 8 * lhi);
           bx[n] = __builtin_bit_cast(
               bf16x8, make_uint4(pack_bf16x2(code_value<MK, 0>(v.x), code_value<MK, 1>(v.x)),
                                  pack_bf16x2(code_value<MK, 2>(v.x), code_value<MK, 3>(v.x)),
                                  pack_bf16x2(code_value<MK, 0>(v.y), code_value<MK, 1>(v.y)),
                                  pack_bf16x2(code_value<MK, 2>(v.y), code_value<MK, 3>(v.y))));
         } else {
-          bx[n] = *reinterpret_cast<const bf16x8*>(smem + C::OFF_X + j * C::RBX + (RX::pos(2 * s + lhi, RX::sw(j)) << 4));
-          bh[n] = *reinterpret_cast<const bf16x8*>(smem + OFF_H + j * C::RBX + (RX::pos(2 * s + lhi, RX::sw(j)) << 4));
+          bx[n] = *reinterpret_cast<const bf16x8*>(smem + C::OFF_X + GT::at(j >> 3, 0, j & 7) + 32 * s + 16 * lhi);
+          bh[n] = *reinterpret_cast<const bf16x8*>(smem + OFF_H + GT::at(j >> 3, 0, j & 7) + 32 * s + 16 * lhi);
         }
       }
 #pragma unroll
@@ -862,35 +890,41 @@ __device__ __forceinline__ void dep_heads4(const AzDevNet& p, uint8_t* smem, con
   if (wave == 1) dep_wdl(p, reinterpret_cast<const float*>(smem + C::OFF_U), value, wdl, b, lane);
 }
 
+// One wave evaluates one board (int8): four such workgroups share a compute unit,
+// one per SIMD, and none waits for another.  The wave owns all five channel blocks
+// and both square blocks.
 template <int MK>
 __global__ __attribute__((amdgpu_flat_work_group_size(64, 64), amdgpu_waves_per_eu(1, 1))) void
-az_dep_kernel(AzDevNet p, const float* __restrict__ planes, const uint8_t* __restrict__ legal,
+az_dep_kernel1(AzDevNet p, const float* __restrict__ planes, const uint8_t* __restrict__ legal,
               float* __restrict__ policy, float* __restrict__ value, float* __restrict__ wdl) {
-  using C = DepCfg<MK>;
+  using C = DepCfg<MK, 1>;
+  using GT = typename C::GT;
+  using GS = typename C::GS;
   using T = typename C::T;
   using frag_t = typename T::frag;
   using acc_t = typename T::acc;
-  using R = Rot<C::RB>;
   constexpr bool QUANT = C::QUANT;
-  constexpr int RB = C::RB, OFF_H = C::OFF_H, OFF_T = C::OFF_T, OFF_Z = C::OFF_Z;
+  static_assert(QUANT, "bf16 boards are evaluated by four waves");
+  constexpr int OFF_H = C::OFF_H, OFF_T = C::OFF_T;
 
-  __shared__ __attribute__((aligned(16))) uint8_t smem[C::SMEM];
+  __shared__ __attribute__((aligned(16))) uint8_t smem[C::OFF_Q4];
+  static_assert(4 * C::OFF_Q4 <= 160 * 1024, "four workgroups per compute unit");
 
-  constexpr int NBW = 2;  // half-board square blocks (the wave owns the whole board)
+  constexpr int NBW = GT::NBK;  // square blocks (the wave owns the whole board)
   const int lane = threadIdx.x;
-  const int l32 = lane & 31, lhi = lane >> 5;
+  const int l32 = lane & 31, lhi = lane >> 5, lr0 = l32 / 8 * GT::NBK;
   const int b = blockIdx.x;
   const int Cin = p.in_planes;
-  const float cap = p.act_cap;
 
-  // residual stream of the board (bf16 networks): h = hi + lo, hi = bf16(h) in
-  // the H buffer (the convolution operand), lo = bf16(h - hi) packed here, two
-  // per register: [block][half][run of 4 channels][2]
-  uint32_t rlo[QUANT ? 1 : DNMB][QUANT ? 1 : NBW][QUANT ? 1 : 8];
-
-  // ---- ingest: zero region, planes -> bf16 [square][64 channels] at OFF_T
-  for (int i = lane; i < C::ZB / 16; i += 64)
-    *reinterpret_cast<i32x4*>(smem + OFF_Z + i * 16) = i32x4{0, 0, 0, 0};
+  // ---- ingest: zero pads, planes -> bf16 [square][64 channels] at OFF_T
+  auto zero_pads = [&](auto geo, int off) {
+    using G = decltype(geo);
+    constexpr int PC = G::ZP / 16;
+    for (int i = lane; i < 8 * PC; i += 64)
+      *reinterpret_cast<i32x4*>(smem + off + i / PC * G::RS + G::PAD + i % PC * 16) = i32x4{0, 0, 0, 0};
+  };
+  zero_pads(GT{}, OFF_H);
+  zero_pads(GS{}, OFF_T);
   {
     // item k = planes 8k..8k+7: lane = square, eight coalesced loads, one
     // 16-byte store
@@ -908,21 +942,21 @@ az_dep_kernel(AzDevNet p, const float* __restrict__ planes, const uint8_t* __res
 #pragma unroll
     for (int ki = 0; ki < KI; ++ki) {
       const int k = ki;
-      *reinterpret_cast<uint4*>(smem + OFF_T + lane * 128 + ((k ^ swz128(lane)) << 4)) =
+      *reinterpret_cast<uint4*>(smem + OFF_T + GS::at(lane >> 3, 0, lane & 7) + 16 * k) =
           make_uint4(pack_bf16x2(pv[ki][0], pv[ki][1]), pack_bf16x2(pv[ki][2], pv[ki][3]),
                      pack_bf16x2(pv[ki][4], pv[ki][5]), pack_bf16x2(pv[ki][6], pv[ki][7]));
     }
   }
 
-  // tower weight ring: K step i of the stream lives in A[i % NBUF].  The stream
-  // is read through a buffer resource: the lane's offset is a constant VGPR, the
-  // step's byte offset a scalar and the block's a literal, so a step's five
-  // loads cost no vector address arithmetic.
-  constexpr int NBUF = C::NBUF;
+  // tower weights: a ring of one group, the three dy of a (dx, channel step), each
+  // loaded two steps ahead.  The stream is read through a buffer resource: the
+  // lane's offset is a constant VGPR, the step's byte offset a scalar, so a step's
+  // five loads cost no vector address arithmetic.
+  constexpr int STEP_BYTES = C::GROUP_BYTES / 3;
   const __amdgpu_buffer_rsrc_t twr = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<void*>(p.tower_w), (short)0, (int)(2 * p.blocks * C::LAYER_BYTES), 0x00020000);
   const int tvoff = lane * T::FB;
-  frag_t A[NBUF][DNMB];
+  frag_t A[3][DNMB];
   auto load_step = [&](frag_t(&dst)[DNMB], int soff) {
 #pragma unroll
     for (int m = 0; m < DNMB; ++m)
@@ -971,38 +1005,35 @@ az_dep_kernel(AzDevNet p, const float* __restrict__ planes, const uint8_t* __res
   }
   __syncthreads();
 
-  // ---- stem: bf16 3x3 conv over 64 (padded) input channels, K = 576
+  // ---- stem: bf16 3x3 conv over 64 (padded) input channels, K = 576, its fp32 sums
+  // in the order (dy, dx, channel step)
   {
     constexpr int SSTEP = DNMB * 64 * 16;  // bytes per K step of the stem stream
     const uint8_t* sw8 = static_cast<const uint8_t*>(p.stem_w) + (size_t)lane * 16;
     f32x16 sacc[DNMB][NBW];
-    // 36 K steps (tap = st / 4, 16 channels each): A fragments of step st in ring
-    // slot st % 4, loaded three steps ahead; B fragments one step ahead
-    constexpr int SR = 4, NST = 9 * DCP / 16;
+    // A fragments in a ring of SR steps, B fragments one step ahead
+    constexpr int SR = 4, CS4 = DCP / 16, NST = 9 * CS4;
     bf16x8 a[SR][DNMB];
     auto load_a = [&](int st) {
+      const int tap = st / CS4, f = (tap % 3 * CS4 + st % CS4) * 3 + tap / 3;
 #pragma unroll
-      for (int m = 0; m < DNMB; ++m) a[st % SR][m] = g_frag<MK_BF16>(sw8 + st * SSTEP + m * 64 * 16);
+      for (int m = 0; m < DNMB; ++m) a[st % SR][m] = g_frag<MK_BF16>(sw8 + f * SSTEP + m * 64 * 16);
     };
-    auto load_b = [&](int st, bf16x8(&dst)[NBW]) {
-      const int tap = st / 4, cs = st % 4, dy = tap / 3 - 1, dx = tap % 3 - 1;
-#pragma unroll
-      for (int n = 0; n < NBW; ++n) {
-        const int j = n * 32 + l32, r = (j >> 3) + dy, c = (j & 7) + dx;
-        const bool ok = (unsigned)r < 8u && (unsigned)c < 8u;
-        const int src = r * 8 + c;
-        const int row = ok ? OFF_T + src * 128 : OFF_Z + ((src * 128) & 255);
-        dst[n] = *reinterpret_cast<const bf16x8*>(smem + row + (((2 * cs + lhi) ^ swz128(src)) << 4));
-      }
+    auto load_b = [&](auto st_c, bf16x8(&dst)[NBW]) {
+      constexpr int st = decltype(st_c)::value, tap = st / CS4, dy = tap / 3 - 1;
+      DTaps<2 * DCP, 1> t;
+      t.init(tap % 3 - 1, l32, lhi);
+      dst[0] = t.template get<bf16x8, dy>(smem + OFF_T, st % CS4);
+      dst[1] = t.template get<bf16x8, 1 + dy>(smem + OFF_T, st % CS4);
     };
 #pragma unroll
     for (int st = 0; st < SR - 1; ++st) load_a(st);
     bf16x8 bcur[NBW], bnext[NBW];
-    load_b(0, bcur);
-#pragma unroll
-    for (int st = 0; st < NST; ++st) {
-      if (st + SR - 1 < NST) load_a(st + SR - 1);
-      if (st + 1 < NST) load_b(st + 1, bnext);
+    load_b(std::integral_constant<int, 0>{}, bcur);
+    static_for<0, NST>([&](auto st_c) {
+      constexpr int st = decltype(st_c)::value;
+      if constexpr (st + SR - 1 < NST) load_a(st + SR - 1);
+      if constexpr (st + 1 < NST) load_b(std::integral_constant<int, (st + 1 < NST ? st + 1 : st)>{}, bnext);
 #pragma unroll
       for (int m = 0; m < DNMB; ++m)
 #pragma unroll
@@ -1010,50 +1041,36 @@ az_dep_kernel(AzDevNet p, const float* __restrict__ planes, const uint8_t* __res
           sacc[m][n] = mma_bf16(a[st % SR][m], bcur[n], st == 0 ? f32x16{} : sacc[m][n]);
 #pragma unroll
       for (int n = 0; n < NBW; ++n) bcur[n] = bnext[n];
-    }
-    // the tower's first weight steps, in flight during the stem's epilogue
-    static_for<0, NBUF - 1>([&](auto i_c) {
-      constexpr int i = decltype(i_c)::value;
-      load_step(A[i], i * C::STEP_BYTES);
     });
-    // epilogue: bias, activation (codes for int8), store in the tower format at OFF_H
+    // the tower's first weight steps, in flight during the stem's epilogue
+    load_step(A[0], 0);
+    load_step(A[1], STEP_BYTES);
+    // epilogue: bias, activation, codes stored at OFF_H
 #pragma unroll
     for (int m = 0; m < DNMB; ++m)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int ch0 = m * 32 + 8 * q + 4 * lhi;
-        const float4 bb = *reinterpret_cast<const float4*>(p.bias + ch0);
-        double mq[4] = {}, bq[4] = {};
-        if constexpr (QUANT) {
+        double mq[4], bq[4];
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            mq[r] = p.qmul[ch0 + r];
-            bq[r] = p.qbias[ch0 + r];
-          }
+        for (int r = 0; r < 4; ++r) {
+          mq[r] = p.qmul[ch0 + r];
+          bq[r] = p.qbias[ch0 + r];
         }
 #pragma unroll
         for (int n = 0; n < NBW; ++n) {
-          const int j = n * 32 + l32;
           const f32x16& v = sacc[m][n];
-          if constexpr (!QUANT) {
-            const float y0 = act_fn(v[4 * q + 0] + bb.x, cap), y1 = act_fn(v[4 * q + 1] + bb.y, cap);
-            const float y2 = act_fn(v[4 * q + 2] + bb.z, cap), y3 = act_fn(v[4 * q + 3] + bb.w, cap);
-            rlo[m][n][2 * q + 0] = pack_bf16x2(y0 - bf16_round(y0), y1 - bf16_round(y1));
-            rlo[m][n][2 * q + 1] = pack_bf16x2(y2 - bf16_round(y2), y3 - bf16_round(y3));
-            *reinterpret_cast<uint2*>(smem + OFF_H + j * RB + (R::pos(ch0 >> 3, R::sw(j)) << 4) + 8 * lhi) =
-                make_uint2(pack_bf16x2(y0, y1), pack_bf16x2(y2, y3));
-          } else {
-            // fp32 sum of the bf16 matrix instruction; rescale and rounding in float64
-            *reinterpret_cast<uint32_t*>(smem + OFF_H + j * RB + (R::pos(ch0 >> 4, R::sw(j)) << 4) + (ch0 & 15)) =
-                pack_codes_d<MK>(__builtin_fma((double)v[4 * q + 0], mq[0], bq[0]),
-                                 __builtin_fma((double)v[4 * q + 1], mq[1], bq[1]),
-                                 __builtin_fma((double)v[4 * q + 2], mq[2], bq[2]),
-                                 __builtin_fma((double)v[4 * q + 3], mq[3], bq[3]), p.qhi[0]);
-          }
+          // fp32 sum of the bf16 matrix instruction; rescale and rounding in float64
+          *reinterpret_cast<uint32_t*>(smem + OFF_H + GT::at(lr0 + n, 0, l32 & 7) + ch0) =
+              pack_codes_d<MK>(__builtin_fma((double)v[4 * q + 0], mq[0], bq[0]),
+                               __builtin_fma((double)v[4 * q + 1], mq[1], bq[1]),
+                               __builtin_fma((double)v[4 * q + 2], mq[2], bq[2]),
+                               __builtin_fma((double)v[4 * q + 3], mq[3], bq[3]), p.qhi[0]);
         }
       }
   }
   __syncthreads();
+  zero_pads(GT{}, OFF_T);
 
   // ---- residual tower
   {
@@ -1062,111 +1079,69 @@ az_dep_kernel(AzDevNet p, const float* __restrict__ planes, const uint8_t* __res
     const int nconv = 2 * p.blocks;
 
     const int l32_ = l32, lhi_ = lhi;
-    auto conv = [&](auto second_c, auto pool_c, auto lb_c, int n_conv) {
-      constexpr bool SECOND = decltype(second_c)::value;
-      constexpr bool POOL = decltype(pool_c)::value;   // first conv of a pooling block
-      constexpr int LB = decltype(lb_c)::value;        // ring slot of the layer's first step
+    // POOL: first convolution of a pooling block; SHORT: its second one, whose
+    // pooled input channels have zero weights: it leaves out the groups past the
+    // last regular one
+    auto conv = [&](auto second_c, auto pool_c, int n_conv) {
+      constexpr bool SECOND = decltype(second_c)::value, PB = decltype(pool_c)::value;
+      constexpr bool POOL = PB && !SECOND, SHORT = PB && SECOND;
       // lane coordinates, opaque to the compiler per layer, so that the layer's
       // many lane-dependent addresses are computed in the layer instead of being
       // hoisted out of the block loop and held (or spilled) across it
       int l32 = l32_, lhi = lhi_;
       asm volatile("" : "+v"(l32), "+v"(lhi));
+      const int lr0 = l32 / 8 * GT::NBK;
       const int wl = n_conv * (int)C::LAYER_BYTES;  // byte offset of the layer in the stream
       const bool has_next = n_conv + 1 < nconv;
-      const int in_off = SECOND ? OFF_T : OFF_H;
-      const int out_off = SECOND ? OFF_H : OFF_T;
+      constexpr int in_off = SECOND ? OFF_T : OFF_H;
+      constexpr int out_off = SECOND ? OFF_H : OFF_T;
       float* kslot = reinterpret_cast<float*>(smem + C::OFF_K + (n_conv & 1) * C::KSLOT);
       // the next layer's epilogue constants, in flight during this layer
       float4 kn[KPL];
       if (has_next) load_consts(n_conv + 2, kn);
-      // B fragments of one K step.  Channel step cs reads logical chunk
-      // lc = 2 cs + lhi of the tap's row, at chunk position (lc + rot) mod NC with
-      // rot the row's rotation: from a per-tap base b0 = row + 16 (lhi + rot) the
-      // address is b0 + 32 cs, except for the last steps, where lc + rot can pass
-      // the row's end and the base is chosen per lane once per tap.
-      constexpr int WRAP0 = (R::NC - 1 - R::RM) / 2;  // first step that can wrap
-      constexpr int NWRAP = CPT > WRAP0 ? CPT - WRAP0 : 0;
-      struct TapRows {
-        int b0[NBW];
-        int bw[NBW][NWRAP > 0 ? NWRAP : 1];
-      };
-      TapRows row, nrow;
-      auto rows_for = [&](int tap, TapRows& tr) {
-        const int dy = tap / 3 - 1, dx = tap % 3 - 1;
+      // groups visited, in order: visit v is group v (SHORT: the last channel step of
+      // a tap left out)
+      constexpr int CPV = SHORT ? (DFR + T::KS - 1) / T::KS : CPT, NV = 3 * CPV;
+      DTaps<C::RB, 1> taps[3];
 #pragma unroll
-        for (int n = 0; n < NBW; ++n) {
-          const int j = n * 32 + l32, r = (j >> 3) + dy, cc = (j & 7) + dx;
-          const bool ok = (unsigned)r < 8u && (unsigned)cc < 8u;
-          const int src = r * 8 + cc;
-          const int ra = in_off + src * RB, rz = OFF_Z + ((src * RB) & 255);
-          const int msk = -(int)ok;
-          const int x = lhi + R::sw(src);
-          tr.b0[n] = ((ra & msk) | (rz & ~msk)) + 16 * x;
-#pragma unroll
-          for (int k = 0; k < NWRAP; ++k)
-            tr.bw[n][k] = tr.b0[n] - (2 * (WRAP0 + k) + x >= R::NC ? 16 * R::NC : 0);
-        }
+      for (int dx = 0; dx < 3; ++dx) taps[dx].init(dx - 1, l32, lhi);
+      frag_t x[GT::NX], xn[GT::NX];
+      auto load_x = [&](auto v_c, frag_t(&dst)[GT::NX]) {
+        constexpr int v = decltype(v_c)::value;
+        static_for<0, GT::NX>([&](auto i_c) {
+          constexpr int i = decltype(i_c)::value;
+          dst[i] = taps[v / CPV].template get<frag_t, i - GT::X0>(smem + in_off, v % CPV);
+        });
       };
-      auto load_b = [&](const TapRows& tr, auto cs_c, frag_t(&dst)[NBW]) {
-        constexpr int cs = decltype(cs_c)::value;
-#pragma unroll
-        for (int n = 0; n < NBW; ++n) {
-          int base;
-          if constexpr (cs >= WRAP0) base = tr.bw[n][cs - WRAP0];
-          else base = tr.b0[n];
-          dst[n] = *reinterpret_cast<const frag_t*>(smem + base + 32 * cs);
-        }
-      };
-      frag_t bc[NBW], bn[NBW];
-      rows_for(0, row);
-      load_b(row, std::integral_constant<int, 0>{}, bc);
-
-      // one tap: CPT K steps; R0 = ring slot of its first step
-      auto tap_body = [&](auto r0_c, auto first_c, int tap) {
-        constexpr int R0 = decltype(r0_c)::value;
-        constexpr bool FIRST = decltype(first_c)::value;
-        rows_for(tap + 1, nrow);
-        static_for<0, CPT>([&](auto cs_c) {
-          constexpr int cs = decltype(cs_c)::value;
-          constexpr int cur = (R0 + cs) % NBUF;
-          {
-            // step tap*CPT + cs + NBUF-1 of this layer (of the next layer past its end;
-            // past the network's last layer this layer is re-read and never used)
-            const int gi = tap * CPT + cs + NBUF - 1;
-            load_step(A[(cur + NBUF - 1) % NBUF], wl + ((has_next || gi < C::S) ? gi * C::STEP_BYTES : 0));
-          }
-          if constexpr (cs + 1 < CPT) load_b(row, std::integral_constant<int, cs + 1>{}, bn);
-          else load_b(nrow, std::integral_constant<int, 0>{}, bn);
+      load_x(std::integral_constant<int, 0>{}, x);
+      static_for<0, NV>([&](auto v_c) {
+        constexpr int v = decltype(v_c)::value;
+        static_for<0, 3>([&](auto d_c) {
+          constexpr int d = decltype(d_c)::value, s2 = 3 * v + d + 2, v2 = s2 / 3;  // two steps ahead
+          // past the layer's end the next layer's first steps (past the network's last
+          // layer this layer is re-read and never used)
+          constexpr int g2 = v2 < NV ? v2 / CPV * CPT + v2 % CPV : v2 - NV;
+          load_step(A[(d + 2) % 3], (v2 < NV ? wl : has_next ? wl + (int)C::LAYER_BYTES : wl) + (3 * g2 + s2 % 3) * STEP_BYTES);
+          if constexpr (d == 0 && v + 1 < NV) load_x(std::integral_constant<int, (v + 1 < NV ? v + 1 : v)>{}, xn);
 #pragma unroll
           for (int m = 0; m < DNMB; ++m)
 #pragma unroll
             for (int n = 0; n < NBW; ++n)
-              c[m][n] = T::mma(A[cur][m], bc[n], (FIRST && cs == 0) ? acc_t{} : c[m][n]);
-#pragma unroll
-          for (int n = 0; n < NBW; ++n) bc[n] = bn[n];
-          // each MFMA followed by one of the next step's LDS reads, then by one of
+              c[m][n] = T::mma(A[d][m], x[n + d], (v == 0 && d == 0) ? acc_t{} : c[m][n]);
+          // each MFMA followed by one of the next group's LDS reads, then by one of
           // the prefetched step's weight loads
           static_for<0, DNMB * 2>([&](auto i_c) {
             constexpr int i = decltype(i_c)::value;
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            if constexpr (i < NBW) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            if constexpr (d == 0 && i < GT::NX && v + 1 < NV) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
             if constexpr (i < DNMB) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
           });
+          __builtin_amdgcn_sched_barrier(0);
         });
-        row = nrow;
-      };
-      constexpr int U = NBUF / gcd_c(CPT, NBUF), NIT = 8 / U, REM = 8 % U;
-      tap_body(std::integral_constant<int, LB>{}, std::true_type{}, 0);
-#pragma nounroll
-      for (int it = 0; it < NIT; ++it) {
-        static_for<0, U>([&](auto u_c) {
-          constexpr int u = decltype(u_c)::value;
-          tap_body(std::integral_constant<int, (LB + (1 + u) * CPT) % NBUF>{}, std::false_type{}, 1 + it * U + u);
-        });
-      }
-      static_for<0, REM>([&](auto u_c) {
-        constexpr int u = decltype(u_c)::value, t = 1 + NIT * U + u;
-        tap_body(std::integral_constant<int, (LB + t * CPT) % NBUF>{}, std::false_type{}, t);
+        if constexpr (v + 1 < NV) {
+#pragma unroll
+          for (int i = 0; i < GT::NX; ++i) x[i] = xn[i];
+        }
       });
 
       // global pooling: pooled channels' board mean and maximum, projected to a
@@ -1175,25 +1150,21 @@ az_dep_kernel(AzDevNet p, const float* __restrict__ planes, const uint8_t* __res
       if constexpr (POOL) {
         // (1) the pooled channels to LDS as [pooled channel][square] in the T
         //     buffer (written by this layer's epilogue only afterwards); rows of
-        //     256 bytes with 16-byte chunks XOR-swizzled by the row.  int8: the
-        //     exact accumulators, activated in float64 in (2); bf16: act(acc + b1)
+        //     256 bytes with 16-byte chunks XOR-swizzled by the row: the exact
+        //     accumulators, activated in float64 in (2)
         float* pt = reinterpret_cast<float*>(smem + OFF_T);
         static_assert(DG * 64 * 4 <= C::BUF, "pooled activations fit in the T buffer");
         static_for<0, DNMB * 4>([&](auto k_c) {
           constexpr int k = decltype(k_c)::value, m = k / 4, q = k % 4;
           if constexpr (32 * m + 8 * q >= DFR) {
             const int ch0 = 32 * m + 8 * q + 4 * lhi;
-            float4 bb = make_float4(0.f, 0.f, 0.f, 0.f);
-            if constexpr (!QUANT) bb = *reinterpret_cast<const float4*>(kslot + ch0);
-            const float bv[4] = {bb.x, bb.y, bb.z, bb.w};
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
               const int pc = ch0 + r - DFR;
 #pragma unroll
               for (int n = 0; n < NBW; ++n) {
-                const int sq = 32 * n + l32, idx = pc * 64 + (((sq >> 2) ^ (pc & 15)) << 2) + (sq & 3);
-                if constexpr (QUANT) reinterpret_cast<int*>(pt)[idx] = (int)c[m][n][4 * q + r];
-                else pt[idx] = med3(c[m][n][4 * q + r] + bv[r], 0.0f, cap);
+                const int sq = (lr0 + n) * 8 + (l32 & 7), idx = pc * 64 + (((sq >> 2) ^ (pc & 15)) << 2) + (sq & 3);
+                reinterpret_cast<int*>(pt)[idx] = c[m][n][4 * q + r];
               }
             }
           }
@@ -1243,58 +1214,39 @@ az_dep_kernel(AzDevNet p, const float* __restrict__ planes, const uint8_t* __res
         // regular channel o's bias takes c[o] (int8: in code units, c[o] / a[n+1])
         add_context<QUANT>(p, kslot, lane, c0, n_conv);
         if (lane + 64 < DFR) add_context<QUANT>(p, kslot, lane + 64, c1, n_conv);
+        zero_pads(GT{}, OFF_T);  // (1) wrote over them
         wave_lds_sync();
       }
 
       // epilogue: per run of 4 channels; LDS reads of constants (and residual
       // codes) issued two runs ahead
-      float hi = 0.0f;
-      double rq = 0.0;
-      if constexpr (QUANT) {
-        const double* kd = reinterpret_cast<const double*>(kslot);
-        hi = (float)kd[2 * DF + 1];
-        rq = SECOND ? kd[2 * DF] : 0.0;
-      }
+      const double* kd = reinterpret_cast<const double*>(kslot);
+      const float hi = (float)kd[2 * DF + 1];
+      const double rq = SECOND ? kd[2 * DF] : 0.0;
       constexpr int NRUN = DNMB * 4, EP_AHEAD = 2, EP_RING = EP_AHEAD + 1;
-      constexpr bool RCODE = QUANT && SECOND;   // residual codes, read in place
-      constexpr bool RHI = !QUANT && SECOND;    // residual hi parts, read in place
-      // int8 constants: qbias and qmul of the run's four channels, float64
+      // qbias and qmul of the run's four channels, float64, and (second convolutions)
+      // the residual codes, read in place
       struct KQ { double b[4], m[4]; };
-      float4 kb[QUANT ? 1 : EP_RING];
-      KQ kq[QUANT ? EP_RING : 1];
-      uint32_t rcode[RCODE ? EP_RING : 1][NBW];
-      uint2 rhi[RHI ? EP_RING : 1][NBW];
+      KQ kq[EP_RING];
+      uint32_t rcode[SECOND ? EP_RING : 1][NBW];
       auto ep_addr = [&](int m, int q, int n) {
-        const int j = n * 32 + l32;
-        const int ch0 = m * 32 + 8 * q + 4 * lhi;
-        const int rowo = out_off + j * RB;
-        if constexpr (QUANT) return rowo + (R::pos(ch0 >> 4, R::sw(j)) << 4) + (ch0 & 15);
-        else return rowo + (R::pos(ch0 >> 3, R::sw(j)) << 4) + 8 * lhi;
+        return out_off + GT::at(lr0 + n, 0, l32 & 7) + m * 32 + 8 * q + 4 * lhi;
       };
       auto ep_load = [&](auto k_c) {
         constexpr int k = decltype(k_c)::value, m = k / 4, q = k % 4, slot = k % EP_RING;
         const int ch0 = m * 32 + 8 * q + 4 * lhi;
-        if constexpr (QUANT) {
-          const double* kd = reinterpret_cast<const double*>(kslot);
 #pragma unroll
-          for (int r = 0; r < 4; r += 2) {
-            const double2 b2 = *reinterpret_cast<const double2*>(kd + ch0 + r);
-            const double2 m2 = *reinterpret_cast<const double2*>(kd + DF + ch0 + r);
-            kq[slot].b[r] = b2.x;
-            kq[slot].b[r + 1] = b2.y;
-            kq[slot].m[r] = m2.x;
-            kq[slot].m[r + 1] = m2.y;
-          }
-        } else {
-          kb[slot] = *reinterpret_cast<const float4*>(kslot + ch0);
+        for (int r = 0; r < 4; r += 2) {
+          const double2 b2 = *reinterpret_cast<const double2*>(kd + ch0 + r);
+          const double2 m2 = *reinterpret_cast<const double2*>(kd + DF + ch0 + r);
+          kq[slot].b[r] = b2.x;
+          kq[slot].b[r + 1] = b2.y;
+          kq[slot].m[r] = m2.x;
+          kq[slot].m[r + 1] = m2.y;
         }
-        if constexpr (RCODE) {
+        if constexpr (SECOND) {
 #pragma unroll
           for (int n = 0; n < NBW; ++n) rcode[slot][n] = *reinterpret_cast<const uint32_t*>(smem + ep_addr(m, q, n));
-        }
-        if constexpr (RHI) {
-#pragma unroll
-          for (int n = 0; n < NBW; ++n) rhi[slot][n] = *reinterpret_cast<const uint2*>(smem + ep_addr(m, q, n));
         }
       };
       static_for<0, EP_AHEAD>([&](auto k_c) { ep_load(k_c); });
@@ -1303,22 +1255,569 @@ az_dep_kernel(AzDevNet p, const float* __restrict__ planes, const uint8_t* __res
         if constexpr (k + EP_AHEAD < NRUN) ep_load(std::integral_constant<int, k + EP_AHEAD>{});
 #pragma unroll
         for (int n = 0; n < NBW; ++n) {
-          const int addr = ep_addr(m, q, n);
           const acc_t& v = c[m][n];
+          // float64 requantisation: z = acc * qmul + qbias (+ residual code * qres)
+          const KQ& kk = kq[slot];
+          double z[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) z[r] = __builtin_fma((double)v[4 * q + r], kk.m[r], kk.b[r]);
+          if constexpr (SECOND) {
+            const uint32_t rc = rcode[slot][n];
+            z[0] = __builtin_fma(code_value_d<MK, 0>(rc), rq, z[0]);
+            z[1] = __builtin_fma(code_value_d<MK, 1>(rc), rq, z[1]);
+            z[2] = __builtin_fma(code_value_d<MK, 2>(rc), rq, z[2]);
+            z[3] = __builtin_fma(code_value_d<MK, 3>(rc), rq, z[3]);
+          }
+          *reinterpret_cast<uint32_t*>(smem + ep_addr(m, q, n)) = pack_codes_d<MK>(z[0], z[1], z[2], z[3], hi);
+        }
+      });
+      if (has_next) store_consts((n_conv + 1) & 1, kn);
+      __syncthreads();
+    };
+
+    for (int blk = 0; blk < p.blocks; ++blk) {
+      const bool pool = p.pool_every > 0 && blk % p.pool_every == p.pool_every - 1;
+      if (pool) {
+        conv(std::false_type{}, std::true_type{}, 2 * blk);
+        conv(std::true_type{}, std::true_type{}, 2 * blk + 1);
+      } else {
+        conv(std::false_type{}, std::false_type{}, 2 * blk);
+        conv(std::true_type{}, std::false_type{}, 2 * blk + 1);
+      }
+    }
+  }
+  dep_heads<MK, 1>(p, smem, legal, policy, value, wdl, b, 0, true, lane);
+}
+
+// Four waves evaluate the workgroup's BPG boards (1 or 2).  Wave w owns every square
+// block of channel block w (0..3) and a share of channel block 4: with two boards
+// square block w, with one (two blocks) waves 0 and 1 have one each.  NBUF: weight
+// ring in groups, SR: the stem's in steps.  Measured (us, NBUF 3 / 5): int8 one
+// board 141 / 140, bf16 one board 204 / 207, two boards 294 / 299.
+template <int MK, int BPG, int NBUF, int SR>
+__global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(1, 1))) void
+az_dep_kernel(AzDevNet p, const float* __restrict__ planes, const uint8_t* __restrict__ legal, int B,
+              float* __restrict__ policy, float* __restrict__ value, float* __restrict__ wdl) {
+  using C = DepCfg<MK, BPG>;
+  using T = typename C::T;
+  using GT = typename C::GT;
+  using GS = typename C::GS;
+  using frag_t = typename T::frag;
+  using acc_t = typename T::acc;
+  constexpr bool QUANT = C::QUANT;
+  constexpr int OFF_H = C::OFF_H, OFF_T = C::OFF_T, NBK = GT::NBK;
+  constexpr int NWV = 4, NT = 64 * NWV;
+  static_assert(DNMB == NWV + 1, "four waves, five channel blocks");
+
+  __shared__ __attribute__((aligned(16))) uint8_t smem[C::SMEM];
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, lhi = lane >> 5;
+  const int b0 = blockIdx.x * BPG;
+  const int Cin = p.in_planes;
+  const float cap = p.act_cap;
+  // this lane's column of a square block: place v in a row, first row r0
+  const int lv = l32 % (8 * BPG), lr0 = l32 / (8 * BPG) * NBK;
+
+  // ---- ingest: zero pads, planes -> bf16 [square][64 channels] at OFF_T.  The T
+  // buffer's own pads, some inside the stem input, are cleared after the stem.
+  auto zero_pads = [&](auto geo, int off) {
+    using G = decltype(geo);
+    constexpr int PC = G::ZP / 16;
+    for (int i = tid; i < 8 * PC; i += NT)
+      *reinterpret_cast<i32x4*>(smem + off + i / PC * G::RS + G::PAD + i % PC * 16) = i32x4{0, 0, 0, 0};
+  };
+  zero_pads(GT{}, OFF_H);
+  zero_pads(GS{}, OFF_T);
+  {
+    // item = planes 8k..8k+7 of one board: lane = square, eight coalesced loads,
+    // one 16-byte store; unconditional loads (clamped to plane 0 of board 0)
+    constexpr int KI = DCP / 8, ITEMS = BPG * KI, PER = ITEMS / NWV;
+    static_assert(ITEMS % NWV == 0, "ingest items per wave");
+    float pv[PER][8];
+#pragma unroll
+    for (int it = 0; it < PER; ++it)
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const int item = wave + NWV * it, b = b0 + item / KI, c = 8 * (item % KI) + t;
+        const bool ok = b < B && c < Cin;
+        const float x = planes[ok ? ((size_t)b * Cin + c) * 64 + lane : (size_t)lane];
+        pv[it][t] = ok ? x : 0.0f;
+      }
+#pragma unroll
+    for (int it = 0; it < PER; ++it) {
+      const int item = wave + NWV * it;
+      *reinterpret_cast<uint4*>(smem + OFF_T + GS::at(lane >> 3, item / KI, lane & 7) + 16 * (item % KI)) =
+          make_uint4(pack_bf16x2(pv[it][0], pv[it][1]), pack_bf16x2(pv[it][2], pv[it][3]),
+                     pack_bf16x2(pv[it][4], pv[it][5]), pack_bf16x2(pv[it][6], pv[it][7]));
+    }
+  }
+
+  // tower weight stream, read through a buffer resource: the lane's offsets (its
+  // own block, and block 4) are constant VGPRs and a fragment's byte offset a
+  // scalar, so the loads cost no vector address arithmetic.  Group g of a layer
+  // (the three dy of one (dx, channel step)) lives in ring slot g % NBUF, loaded
+  // NBUF - 1 groups ahead, across layers.
+  const __amdgpu_buffer_rsrc_t twr = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<void*>(p.tower_w), (short)0, (int)(2 * p.blocks * C::LAYER_BYTES), 0x00020000);
+  const int tvoff = (wave * 64 + lane) * T::FB, tvoffx = ((DNMB - 1) * 64 + lane) * T::FB;
+  // per-layer epilogue constants of conv index k (0 = stem), one 16-byte chunk per
+  // thread, loaded at the start of a layer and parked in LDS before its barrier
+  constexpr int KV = C::KSLOT / 16;
+  static_assert(KV <= NT, "constant staging");
+  auto load_consts = [&](int k) -> float4 {
+    if (tid >= KV) return make_float4(0.f, 0.f, 0.f, 0.f);
+    const void* src;
+    if constexpr (QUANT)
+      src = tid < DF / 2 ? p.qbias + (size_t)k * DF + 2 * tid
+            : tid < DF   ? p.qmul + (size_t)k * DF + 2 * (tid - DF / 2)
+                         : p.qext + 2 * (size_t)k;
+    else src = p.bias + (size_t)k * DF + 4 * tid;
+    return *reinterpret_cast<const float4*>(src);
+  };
+  auto store_consts = [&](int slot, const float4& v) {
+    if (tid < KV) *reinterpret_cast<float4*>(smem + C::OFF_K + slot * C::KSLOT + 16 * tid) = v;
+  };
+  // head constants, staged once: embedding row scale and bias, query and key biases
+  {
+    float* hc = reinterpret_cast<float*>(smem + C::OFF_HC);
+    if (tid < AZ_DEP_EMB_ROWS) {
+      hc[tid] = p.emb_sc[tid];
+      hc[AZ_DEP_EMB_ROWS + tid] = p.emb_bc[tid];
+    }
+    if (tid < DD) {
+      hc[2 * AZ_DEP_EMB_ROWS + tid] = p.q_b[tid];
+      hc[2 * AZ_DEP_EMB_ROWS + DD + tid] = p.k_b[tid];
+    }
+  }
+  store_consts(0, load_consts(1));
+
+  // ---- stem and tower of one wave.  XB: its square blocks of channel block 4 (the
+  // second tile set); with one board XN is that block's index, else the blocks are
+  // wave * XB ..  Every wave meets the same sequence of workgroup barriers.
+  auto trunk = [&](auto xb_c, auto xn_c) {
+    constexpr int XB = decltype(xb_c)::value, XN = decltype(xn_c)::value;
+    constexpr int NAF = XB > 0 ? 2 : 1;  // weight fragments per K step
+    constexpr int XBn = XB > 0 ? XB : 1;
+    const int xfirst = BPG == 1 ? XN : wave * XB;
+    // lane rows of the second set's fragments of one horizontal tap (several boards):
+    // blocks xfirst - 1, xfirst .., xfirst + XB
+    struct XRows { int lo, mid, hi; };
+    auto x_rows = [&](const auto& t) {
+      using G = typename std::decay_t<decltype(t)>::G;
+      XRows r;
+      r.mid = t.row + xfirst * G::RS;
+      r.lo = xfirst == 0 ? t.lo : r.mid - G::RS;
+      r.hi = xfirst + XBn == NBK ? t.hi : r.mid + XBn * G::RS;
+      return r;
+    };
+
+    // residual stream of the boards (bf16 networks): h = hi + lo, hi = bf16(h) in
+    // the H buffer (the convolution operand), lo = bf16(h - hi) packed here, two
+    // per register: [square block][run of 4 channels][2]
+    uint32_t rlo[QUANT ? 1 : NBK][QUANT ? 1 : 8], rlox[QUANT ? 1 : XBn][QUANT ? 1 : 8];
+
+    // B fragments of one (dx, channel step): every block's, and the second set's
+    // with several boards (its blocks differ by wave, so they have no fixed place
+    // among the first)
+    constexpr bool XF = XB > 0 && BPG > 1;
+    auto load_x = [&](const auto& t, const XRows& xr, const uint8_t* buf, int cs, auto& x, auto& xx) {
+      using G = typename std::decay_t<decltype(t)>::G;
+      using Frag = std::decay_t<decltype(x[0])>;
+      static_for<0, G::NX>([&](auto i_c) {
+        constexpr int i = decltype(i_c)::value;
+        x[i] = t.template get<Frag, i - G::X0>(buf, cs);
+      });
+      if constexpr (XF) {
+        xx[0] = *reinterpret_cast<const Frag*>(buf + xr.lo + 32 * cs);
+#pragma unroll
+        for (int k = 0; k < XB; ++k) xx[1 + k] = *reinterpret_cast<const Frag*>(buf + k * G::RS + xr.mid + 32 * cs);
+        xx[1 + XB] = *reinterpret_cast<const Frag*>(buf + xr.hi + 32 * cs);
+      }
+    };
+    // every product of one (dx, channel step), each accumulator in the order of dy
+    auto products = [&](auto mk_c, auto first_c, const auto& a, const auto& x, const auto& xx, auto& acc, auto& accx) {
+      using M = Mk<decltype(mk_c)::value>;
+      constexpr bool FIRST = decltype(first_c)::value;
+      constexpr int X0 = GT::X0, NX = GT::NX;
+      static_for<0, 3>([&](auto d_c) {
+        constexpr int d = decltype(d_c)::value;
+        static_for<0, NBK>([&](auto j_c) {
+          constexpr int j = decltype(j_c)::value, xi = j + d - 1 + X0;
+          if constexpr (xi >= 0 && xi < NX) {
+            constexpr bool zero = FIRST && (d == 0 || (X0 == 0 && d == 1 && j == 0));
+            acc[j] = M::mma(a[d][0], x[xi], zero ? typename M::acc{} : acc[j]);
+          }
+        });
+        if constexpr (XB > 0) {
+#pragma unroll
+          for (int k = 0; k < XB; ++k) {
+            constexpr int xn = XN + (GT::X0 - 1);
+            if constexpr (XF) accx[k] = M::mma(a[d][NAF - 1], xx[k + d], FIRST && d == 0 ? typename M::acc{} : accx[k]);
+            else accx[k] = M::mma(a[d][NAF - 1], x[xn + d], FIRST && d == 0 ? typename M::acc{} : accx[k]);
+          }
+        }
+      });
+    };
+    constexpr int NXX = XF ? XB + 2 : 1;
+    constexpr int NMF = 3 * NBK - (GT::EDGE ? 0 : 2) + 3 * XB, NDS = GT::NX + (XF ? XB + 2 : 0), NVM = 3 * NAF;
+    auto interleave = [&](auto lds_c, auto vm_c) {
+      // each MFMA is followed by one of the next step's LDS reads, then by one of
+      // the prefetched group's weight loads; a step is one scheduling region
+      constexpr bool LDS = decltype(lds_c)::value, VM = decltype(vm_c)::value;
+      static_for<0, NMF>([&](auto i_c) {
+        constexpr int i = decltype(i_c)::value;
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        if constexpr (LDS && i < NDS) __builtin_amdgcn_sched_group_barrier(0x100, i + 1 == NMF ? NDS - i : 1, 0);
+        if constexpr (VM && i < NVM) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+      });
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    // the lane's coordinates in the epilogues, opaque to the compiler in every layer:
+    // hoisted out of the block loop, the epilogues' addresses would spill
+    int elh = lhi, elv = lv, elr = lr0;
+    // first channel of run q (four channels 8q + 4 lhi ..) of tile set m
+    auto ch_of = [&](int m, int q) { return (m == 0 ? wave : DNMB - 1) * 32 + 8 * q + 4 * elh; };
+    // LDS address of a run of square block n
+    auto run_addr = [&](int off, int ch0, int n) { return off + (elr + n) * GT::RS + elv * GT::CS + ch0 * T::ES; };
+
+    frag_t A[NBUF][3][NAF];
+    auto load_group = [&](frag_t(&dst)[3][NAF], int soff) {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        const int o = soff + d * DNMB * 64 * T::FB;
+        dst[d][0] = __builtin_bit_cast(frag_t, __builtin_amdgcn_raw_buffer_load_b128(twr, tvoff, o, 0));
+        if constexpr (NAF > 1) dst[d][1] = __builtin_bit_cast(frag_t, __builtin_amdgcn_raw_buffer_load_b128(twr, tvoffx, o, 0));
+      }
+    };
+
+    // ---- stem: bf16 3x3 conv over 64 (padded) input channels.  Its fp32 sums run
+    // in the order (dy, dx, channel step): the unnormalised count planes round in
+    // them, and another order moves a stem code in about every second batch of
+    // 1,024.  36 K steps, each reading its own fragments (4% of the products).
+    {
+      constexpr int CS4 = DCP / 16, SN = 9 * CS4;
+      const uint8_t* sw8 = static_cast<const uint8_t*>(p.stem_w) + (size_t)lane * 16;
+      // A fragments in a ring of SR steps, the first ones loaded before the barrier
+      bf16x8 a[SR][NAF];
+      auto load_a = [&](int st) {
+        const int tap = st / CS4, f = (tap % 3 * CS4 + st % CS4) * 3 + tap / 3;
+#pragma unroll
+        for (int m = 0; m < NAF; ++m)
+          a[st % SR][m] = g_frag<MK_BF16>(sw8 + (f * DNMB + (m == 0 ? wave : DNMB - 1)) * 64 * 16);
+      };
+#pragma unroll
+      for (int st = 0; st < SR - 1; ++st) load_a(st);
+      __syncthreads();  // the ingest's planes and constants are in LDS
+      f32x16 sacc[NBK], saccx[XBn];
+      bf16x8 x[NBK], xx[XBn], xn[NBK], xxn[XBn];
+      auto load_s = [&](auto st_c, auto& d0, auto& d1) {
+        constexpr int st = decltype(st_c)::value, dx = st / CS4 % 3, dy = st / CS4 / 3 - 1, cs = st % CS4;
+        DTaps<2 * DCP, BPG> t;
+        t.init(dx - 1, l32, lhi);
+        const uint8_t* buf = smem + OFF_T;
+        static_for<0, NBK>([&](auto j_c) {
+          constexpr int j = decltype(j_c)::value;
+          d0[j] = t.template get<bf16x8, j + dy>(buf, cs);
+        });
+        if constexpr (XB > 0 && BPG == 1) d1[0] = t.template get<bf16x8, XN + dy>(buf, cs);
+        if constexpr (XF) {
+          const XRows xr = x_rows(t);
+#pragma unroll
+          for (int k = 0; k < XB; ++k) {
+            const int r = k + dy < 0 ? xr.lo : k + dy >= XB ? xr.hi : xr.mid + (k + dy) * GS::RS;
+            d1[k] = *reinterpret_cast<const bf16x8*>(buf + r + 32 * cs);
+          }
+        }
+      };
+      load_s(std::integral_constant<int, 0>{}, x, xx);
+      static_for<0, SN>([&](auto st_c) {
+        constexpr int st = decltype(st_c)::value;
+        if constexpr (st + SR - 1 < SN) load_a(st + SR - 1);
+        if constexpr (st + 1 < SN) load_s(std::integral_constant<int, st + 1>{}, xn, xxn);
+#pragma unroll
+        for (int j = 0; j < NBK; ++j) sacc[j] = mma_bf16(a[st % SR][0], x[j], st == 0 ? f32x16{} : sacc[j]);
+#pragma unroll
+        for (int k = 0; k < XB; ++k) saccx[k] = mma_bf16(a[st % SR][NAF - 1], xx[k], st == 0 ? f32x16{} : saccx[k]);
+        if constexpr (st + 1 < SN) {
+#pragma unroll
+          for (int j = 0; j < NBK; ++j) x[j] = xn[j];
+#pragma unroll
+          for (int k = 0; k < XBn; ++k) xx[k] = xxn[k];
+        }
+        if constexpr (st % CS4 == CS4 - 1) __builtin_amdgcn_sched_barrier(0);
+      });
+      // the tower's first weight groups, in flight during the stem's epilogue
+      static_for<0, NBUF - 1>([&](auto i_c) {
+        constexpr int i = decltype(i_c)::value;
+        load_group(A[i], i * C::GROUP_BYTES);
+      });
+      // epilogue: bias, activation (codes for int8), store in the tower format at OFF_H
+      auto put = [&](int m, int q, int n, const f32x16& v, uint32_t(&rl)[QUANT ? 1 : 8], const float4& bb,
+                     const double(&mq)[4], const double(&bq)[4]) {
+        const int addr = run_addr(OFF_H, ch_of(m, q), n);
+        if constexpr (!QUANT) {
+          const float y0 = act_fn(v[4 * q + 0] + bb.x, cap), y1 = act_fn(v[4 * q + 1] + bb.y, cap);
+          const float y2 = act_fn(v[4 * q + 2] + bb.z, cap), y3 = act_fn(v[4 * q + 3] + bb.w, cap);
+          rl[2 * q + 0] = pack_bf16x2(y0 - bf16_round(y0), y1 - bf16_round(y1));
+          rl[2 * q + 1] = pack_bf16x2(y2 - bf16_round(y2), y3 - bf16_round(y3));
+          *reinterpret_cast<uint2*>(smem + addr) = make_uint2(pack_bf16x2(y0, y1), pack_bf16x2(y2, y3));
+        } else {
+          // fp32 sum of the bf16 matrix instruction; rescale and rounding in float64
+          *reinterpret_cast<uint32_t*>(smem + addr) =
+              pack_codes_d<MK>(__builtin_fma((double)v[4 * q + 0], mq[0], bq[0]),
+                               __builtin_fma((double)v[4 * q + 1], mq[1], bq[1]),
+                               __builtin_fma((double)v[4 * q + 2], mq[2], bq[2]),
+                               __builtin_fma((double)v[4 * q + 3], mq[3], bq[3]), p.qhi[0]);
+        }
+      };
+#pragma unroll
+      for (int m = 0; m < NAF; ++m)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int ch0 = ch_of(m, q);
+          const float4 bb = *reinterpret_cast<const float4*>(p.bias + ch0);
+          double mq[4] = {}, bq[4] = {};
+          if constexpr (QUANT) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              mq[r] = p.qmul[ch0 + r];
+              bq[r] = p.qbias[ch0 + r];
+            }
+          }
+          if (m == 0) {
+#pragma unroll
+            for (int n = 0; n < NBK; ++n) put(m, q, n, sacc[n], rlo[QUANT ? 0 : n], bb, mq, bq);
+          } else {
+#pragma unroll
+            for (int k = 0; k < XB; ++k) put(m, q, xfirst + k, saccx[k], rlox[QUANT ? 0 : k], bb, mq, bq);
+          }
+        }
+    }
+    __syncthreads();
+    zero_pads(GT{}, OFF_T);  // read after the first layer's barrier
+
+    // ---- residual tower
+    {
+      constexpr int CPT = C::CPT;
+      acc_t c[NBK], cx[XBn];
+      const int nconv = 2 * p.blocks;
+      DTaps<C::RB, BPG> taps[3];
+#pragma unroll
+      for (int dx = 0; dx < 3; ++dx) taps[dx].init(dx - 1, l32, lhi);
+
+      // pool (wave-uniform): the layer is in a pooling block.  One code for both kinds
+      // of block: the four kinds of layer unrolled would pass the instruction cache.
+      auto conv = [&](auto second_c, int n_conv, bool pool) {
+        constexpr bool SECOND = decltype(second_c)::value;
+        constexpr int NS = C::NS;
+        static_assert(NS % NBUF == 0, "every layer starts at ring slot 0");
+        const int wl = n_conv * (int)C::LAYER_BYTES;  // byte offset of the layer in the stream
+        const bool has_next = n_conv + 1 < nconv;
+        constexpr int in_off = SECOND ? OFF_T : OFF_H;
+        constexpr int out_off = SECOND ? OFF_H : OFF_T;
+        uint8_t* kslot = smem + C::OFF_K + (n_conv & 1) * C::KSLOT;
+        // the next layer's epilogue constants, in flight during this layer
+        const float4 kn = has_next ? load_consts(n_conv + 2) : make_float4(0.f, 0.f, 0.f, 0.f);
+        // a pooling layer's projection weights: thread t's output t % 128, all 2g
+        // inputs as [i/4] float4s; with one board in flight during the K loop
+        constexpr int NWP = SECOND ? 1 : 2 * DG / 4;
+        const int po = tid & 127;
+        float4 wpool[NWP];
+        auto load_pool = [&]() {
+          const float4* wt = reinterpret_cast<const float4*>(p.pool_wt) +
+                             (size_t)(n_conv / 2 / p.pool_every) * (2 * DG / 4) * AZ_DEP_POOL_OPAD + po;
+#pragma unroll
+          for (int i4 = 0; i4 < NWP; ++i4) wpool[i4] = wt[(size_t)i4 * AZ_DEP_POOL_OPAD];
+        };
+        if constexpr (!SECOND && BPG == 1) {
+          if (pool) load_pool();
+        }
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx) taps[dx].opaque();
+        asm volatile("" : "+v"(elh), "+v"(elv), "+v"(elr));
+        XRows xr[3];
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx) xr[dx] = x_rows(taps[dx]);
+
+        frag_t x[GT::NX], xx[NXX], xn[GT::NX], xxn[NXX];
+        auto load_s = [&](auto s_c, auto& d0, auto& d1) {
+          constexpr int s = decltype(s_c)::value;
+          load_x(taps[s / CPT], xr[s / CPT], smem + in_off, s % CPT, d0, d1);
+        };
+        load_s(std::integral_constant<int, 0>{}, x, xx);
+        static_for<0, NS>([&](auto s_c) {
+          constexpr int s = decltype(s_c)::value, gi = s + NBUF - 1;
+          // group s + NBUF-1 of this layer, or of the next one past its end; past the
+          // network's last layer this layer is re-read and never used
+          if constexpr (gi < NS) load_group(A[gi % NBUF], wl + gi * C::GROUP_BYTES);
+          else load_group(A[gi % NBUF], has_next ? wl + (int)C::LAYER_BYTES + (gi - NS) * C::GROUP_BYTES : wl);
+          if constexpr (s + 1 < NS) load_s(std::integral_constant<int, s + 1>{}, xn, xxn);
+          // the second convolution of a pooling block has zero weights for the pooled
+          // channels: its steps past the last regular one only pass the ring on
+          constexpr bool REGULAR = !SECOND || s % CPT * T::KS < DFR;
+          if (REGULAR || !pool) {
+            products(std::integral_constant<int, MK>{}, std::integral_constant<bool, s == 0>{}, A[s % NBUF], x, xx, c, cx);
+            interleave(std::integral_constant<bool, (REGULAR && s + 1 < NS)>{}, std::integral_constant<bool, REGULAR>{});
+          }
+          if constexpr (s + 1 < NS) {
+#pragma unroll
+            for (int i = 0; i < GT::NX; ++i) x[i] = xn[i];
+#pragma unroll
+            for (int i = 0; i < NXX; ++i) xx[i] = xxn[i];
+          }
+        });
+
+        // global pooling: per board the pooled channels' mean and maximum, projected
+        // to a context term that joins the regular channels' bias (OFF_PB)
+        if constexpr (!SECOND) {
+         if (pool) {
+          if constexpr (BPG > 1) load_pool();
+          // (1) the pooled channels to LDS as [board][pooled channel][square] in the T
+          //     buffer (written by this layer's epilogue only afterwards); rows of
+          //     256 bytes with 16-byte chunks XOR-swizzled by the row.  int8: the
+          //     exact accumulators, activated in float64 in (2); bf16: act(acc + b1)
+          float* pt = reinterpret_cast<float*>(smem + OFF_T);
+          auto put_pool = [&](int m, int q, int n, const acc_t& v) {
+            const int ch0 = ch_of(m, q);
+            float4 bb = make_float4(0.f, 0.f, 0.f, 0.f);
+            if constexpr (!QUANT) bb = *reinterpret_cast<const float4*>(kslot + 4 * ch0);
+            const float bv[4] = {bb.x, bb.y, bb.z, bb.w};
+            float* ptb = pt + (elv >> 3) * DG * 64;
+            const int sq = (elr + n) * 8 + (elv & 7);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const int pc = ch0 + r - DFR, idx = pc * 64 + (((sq >> 2) ^ (pc & 15)) << 2) + (sq & 3);
+              if constexpr (QUANT) reinterpret_cast<int*>(ptb)[idx] = (int)v[4 * q + r];
+              else ptb[idx] = med3(v[4 * q + r] + bv[r], 0.0f, cap);
+            }
+          };
+          constexpr int Q0 = (DFR - 32 * (DNMB - 2)) / 8;  // block 3's first pooled run
+          if (wave == DNMB - 2) {
+#pragma unroll
+            for (int q = Q0; q < 4; ++q)
+#pragma unroll
+              for (int n = 0; n < NBK; ++n) put_pool(0, q, n, c[n]);
+          }
+          if constexpr (XB > 0) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+              for (int k = 0; k < XB; ++k) put_pool(1, q, xfirst + k, cx[k]);
+          }
+          wave_lds_sync();
+          // (2) thread r < BPG * g: board sum (fp64) and maximum of row r; statistics
+          //     [mean g | max g] per board
+          double* pg = reinterpret_cast<double*>(smem + C::OFF_PG);
+          static_assert(BPG * DG <= NT, "a thread per pooled row");
+          // with one board ten rows per wave, else in thread order
+          const int pr = BPG == 1 ? (lane < DG / 4 ? (DG / 4) * wave + lane : DG) : tid;
+          if (pr < BPG * DG) {
+            const int bd = pr / DG, pc = pr % DG;
+            const double2 mx_sum = pool_row<QUANT>(p, pt + bd * DG * 64, pc, n_conv);
+            pg[bd * 2 * DG + pc] = mx_sum.y * (1.0 / 64.0);
+            pg[bd * 2 * DG + DG + pc] = mx_sum.x;
+          }
+          wave_lds_sync();
+          // (3) c[o] = sum_i Wg[o][i] g[i] in fp64 (fp32 weights are exact): thread
+          //     t takes output t % 128 of boards t / 128, t / 128 + 2; the pooled
+          //     channels keep their bias (their codes are read by nothing)
+          {
+            constexpr int NB2 = BPG > 2 ? 2 : 1;
+            const int bd0 = tid >> 7;
+            double co[NB2] = {};
+            if (bd0 < BPG) {
+#pragma unroll
+              for (int i4 = 0; i4 < NWP; ++i4) {
+                const float4 w = wpool[i4];
+#pragma unroll
+                for (int k = 0; k < NB2; ++k) {
+                  const double* gi = pg + (bd0 + 2 * k) * 2 * DG + 4 * i4;
+                  co[k] = __builtin_fma((double)w.x, gi[0], co[k]);
+                  co[k] = __builtin_fma((double)w.y, gi[1], co[k]);
+                  co[k] = __builtin_fma((double)w.z, gi[2], co[k]);
+                  co[k] = __builtin_fma((double)w.w, gi[3], co[k]);
+                }
+              }
+#pragma unroll
+              for (int k = 0; k < NB2; ++k) {
+                const int bd = bd0 + 2 * k;
+                if constexpr (QUANT) {
+                  const double* kb = reinterpret_cast<const double*>(kslot);
+                  double* pb = reinterpret_cast<double*>(smem + C::OFF_PB) + bd * DF;
+                  pb[po] = po < DFR ? kb[po] + co[k] * p.pool_cinv[n_conv] : kb[po];
+                  if (po < DF - 128) pb[128 + po] = kb[128 + po];
+                } else {
+                  const float* kb = reinterpret_cast<const float*>(kslot);
+                  float* pb = reinterpret_cast<float*>(smem + C::OFF_PB) + bd * DF;
+                  pb[po] = po < DFR ? kb[po] + (float)co[k] : kb[po];
+                  if (po < DF - 128) pb[128 + po] = kb[128 + po];
+                }
+              }
+            }
+          }
+          zero_pads(GT{}, OFF_T);  // (1) wrote over them
+          wave_lds_sync();
+         }
+        }
+
+        // epilogue: per run of 4 channels; LDS reads of constants (and residual codes
+        // or hi parts, read in place) issued two runs ahead
+        const uint8_t* kbias = !SECOND && pool ? smem + C::OFF_PB + (elv >> 3) * DF * C::KE : kslot;
+        float hi = 0.0f;
+        double rq = 0.0;
+        if constexpr (QUANT) {
+          const double* kd = reinterpret_cast<const double*>(kslot);
+          hi = (float)kd[2 * DF + 1];
+          rq = SECOND ? kd[2 * DF] : 0.0;
+        }
+        constexpr int NRUN = NAF * 4, EP_AHEAD = 2, EP_RING = EP_AHEAD + 1;
+        constexpr int NMAX = cmax(NBK, XBn);
+        struct KQ { double b[QUANT ? 4 : 1], m[QUANT ? 4 : 1]; float4 f; };
+        KQ kq[EP_RING];
+        using rin_t = std::conditional_t<QUANT, uint32_t, uint2>;  // codes, or hi parts
+        rin_t rin[SECOND ? EP_RING : 1][SECOND ? NMAX : 1];
+        auto ep_load = [&](auto k_c) {
+          constexpr int k = decltype(k_c)::value, m = k / 4, q = k % 4, slot = k % EP_RING;
+          const int ch0 = ch_of(m, q);
+          if constexpr (QUANT) {
+            const double* kb = reinterpret_cast<const double*>(kbias);
+            const double* kd = reinterpret_cast<const double*>(kslot);
+#pragma unroll
+            for (int r = 0; r < 4; r += 2) {
+              const double2 b2 = *reinterpret_cast<const double2*>(kb + ch0 + r);
+              const double2 m2 = *reinterpret_cast<const double2*>(kd + DF + ch0 + r);
+              kq[slot].b[r] = b2.x;
+              kq[slot].b[r + 1] = b2.y;
+              kq[slot].m[r] = m2.x;
+              kq[slot].m[r + 1] = m2.y;
+            }
+          } else {
+            kq[slot].f = *reinterpret_cast<const float4*>(kbias + 4 * ch0);
+          }
+          if constexpr (SECOND) {
+#pragma unroll
+            for (int n = 0; n < (m == 0 ? NBK : XB); ++n) {
+              const uint8_t* a = smem + run_addr(out_off, ch0, m == 0 ? n : xfirst + n);
+              rin[slot][n] = *reinterpret_cast<const rin_t*>(a);
+            }
+          }
+        };
+        auto ep_run = [&](int q, const KQ& kk, const acc_t& v, int addr, rin_t hv, uint32_t(&rl)[QUANT ? 1 : 8]) {
           if constexpr (!QUANT) {
-            const float4 bb = kb[slot];
-            float y0 = v[4 * q + 0] + bb.x, y1 = v[4 * q + 1] + bb.y;
-            float y2 = v[4 * q + 2] + bb.z, y3 = v[4 * q + 3] + bb.w;
+            float y0 = v[4 * q + 0] + kk.f.x, y1 = v[4 * q + 1] + kk.f.y;
+            float y2 = v[4 * q + 2] + kk.f.z, y3 = v[4 * q + 3] + kk.f.w;
             if constexpr (SECOND) {
               // block input h = hi + lo (exact in fp32)
-              const uint2 hv = rhi[slot][n];
-              const uint32_t l01 = rlo[m][n][2 * q], l23 = rlo[m][n][2 * q + 1];
+              const uint32_t l01 = rl[2 * q], l23 = rl[2 * q + 1];
               y0 = act_fn(y0 + (__uint_as_float(hv.x << 16) + __uint_as_float(l01 << 16)), cap);
               y1 = act_fn(y1 + (__uint_as_float(hv.x & 0xffff0000u) + __uint_as_float(l01 & 0xffff0000u)), cap);
               y2 = act_fn(y2 + (__uint_as_float(hv.y << 16) + __uint_as_float(l23 << 16)), cap);
               y3 = act_fn(y3 + (__uint_as_float(hv.y & 0xffff0000u) + __uint_as_float(l23 & 0xffff0000u)), cap);
-              rlo[m][n][2 * q + 0] = pack_bf16x2(y0 - bf16_round(y0), y1 - bf16_round(y1));
-              rlo[m][n][2 * q + 1] = pack_bf16x2(y2 - bf16_round(y2), y3 - bf16_round(y3));
+              rl[2 * q + 0] = pack_bf16x2(y0 - bf16_round(y0), y1 - bf16_round(y1));
+              rl[2 * q + 1] = pack_bf16x2(y2 - bf16_round(y2), y3 - bf16_round(y3));
             } else {
               y0 = act_fn(y0, cap);
               y1 = act_fn(y1, cap);
@@ -1328,629 +1827,89 @@ az_dep_kernel(AzDevNet p, const float* __restrict__ planes, const uint8_t* __res
             *reinterpret_cast<uint2*>(smem + addr) = make_uint2(pack_bf16x2(y0, y1), pack_bf16x2(y2, y3));
           } else {
             // float64 requantisation: z = acc * qmul + qbias (+ residual code * qres)
-            const KQ& kk = kq[slot];
             double z[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) z[r] = __builtin_fma((double)v[4 * q + r], kk.m[r], kk.b[r]);
             if constexpr (SECOND) {
-              const uint32_t rc = rcode[slot][n];
-              z[0] = __builtin_fma(code_value_d<MK, 0>(rc), rq, z[0]);
-              z[1] = __builtin_fma(code_value_d<MK, 1>(rc), rq, z[1]);
-              z[2] = __builtin_fma(code_value_d<MK, 2>(rc), rq, z[2]);
-              z[3] = __builtin_fma(code_value_d<MK, 3>(rc), rq, z[3]);
+              z[0] = __builtin_fma(code_value_d<MK, 0>(hv), rq, z[0]);
+              z[1] = __builtin_fma(code_value_d<MK, 1>(hv), rq, z[1]);
+              z[2] = __builtin_fma(code_value_d<MK, 2>(hv), rq, z[2]);
+              z[3] = __builtin_fma(code_value_d<MK, 3>(hv), rq, z[3]);
             }
             *reinterpret_cast<uint32_t*>(smem + addr) = pack_codes_d<MK>(z[0], z[1], z[2], z[3], hi);
           }
-        }
-      });
-      if (has_next) store_consts((n_conv + 1) & 1, kn);
-      __syncthreads();
-    };
-
-    for (int blk = 0; blk < p.blocks; ++blk) {
-      const bool pool = p.pool_every > 0 && blk % p.pool_every == p.pool_every - 1;
-      if (pool) conv(std::false_type{}, std::true_type{}, std::integral_constant<int, 0>{}, 2 * blk);
-      else conv(std::false_type{}, std::false_type{}, std::integral_constant<int, 0>{}, 2 * blk);
-      conv(std::true_type{}, std::false_type{}, std::integral_constant<int, C::S % NBUF>{}, 2 * blk + 1);
-    }
-  }
-
-  // ---- heads input (bf16 networks): the low part h - bf16(h) of the fp32
-  // residual as bf16 rows [square][F] at OFF_X, H holding bf16(h); int8
-  // networks read the final codes from H and convert them in registers
-  using RX = Rot<C::RBX>;
-  if constexpr (!QUANT) {
-#pragma unroll
-    for (int m = 0; m < DNMB; ++m)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int ch0 = m * 32 + 8 * q + 4 * lhi;
-#pragma unroll
-        for (int n = 0; n < NBW; ++n) {
-          const int j = n * 32 + l32;
-          *reinterpret_cast<uint2*>(smem + C::OFF_X + j * C::RBX + (RX::pos(ch0 >> 3, RX::sw(j)) << 4) + 8 * lhi) =
-              make_uint2(rlo[m][n][2 * q], rlo[m][n][2 * q + 1]);
-        }
-      }
-  }
-  __syncthreads();
-
-  dep_heads<MK>(p, smem, legal, policy, value, wdl, b, lane);
-}
-
-template <int MK>
-__global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(1, 1))) void
-az_dep_kernel4(AzDevNet p, const float* __restrict__ planes, const uint8_t* __restrict__ legal,
-              float* __restrict__ policy, float* __restrict__ value, float* __restrict__ wdl) {
-  using C = DepCfg<MK>;
-  using T = typename C::T;
-  using frag_t = typename T::frag;
-  using acc_t = typename T::acc;
-  using R = Rot<C::RB>;
-  constexpr bool QUANT = C::QUANT;
-  constexpr int RB = C::RB, OFF_H = C::OFF_H, OFF_T = C::OFF_T, OFF_Z = C::OFF_Z;
-
-  __shared__ __attribute__((aligned(16))) uint8_t smem[C::SMEM4];
-
-  // Tiles of a layer: five 32-channel blocks x two half-board square blocks.
-  // Wave w (one per SIMD) owns both tiles of block w, and waves 0 and 1 also
-  // tile (4, w), so no SIMD runs more than three of the ten MFMA chains of a K
-  // step.
-  constexpr int NWB = 4;                     // waves per board
-  static_assert(DNMB == NWB + 1, "four waves, five blocks");
-  constexpr int NT = 64 * NWB;
-  constexpr int MBW = 1;                     // blocks whose two tiles the wave owns
-  constexpr int NBW = 2;                     // half-board square blocks
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l32 = lane & 31, lhi = lane >> 5;
-  const int mb0 = wave;                      // first block the wave owns
-  const int b = blockIdx.x;
-  const int Cin = p.in_planes;
-  const float cap = p.act_cap;
-
-  // ---- ingest: zero region, planes -> bf16 [square][64 channels] at OFF_T
-  for (int i = tid; i < C::ZB / 16; i += NT)
-    *reinterpret_cast<i32x4*>(smem + OFF_Z + i * 16) = i32x4{0, 0, 0, 0};
-  {
-    // item k = planes 8k..8k+7 (items wave, wave + NWB, ...): lane = square,
-    // eight coalesced loads, one 16-byte store
-    constexpr int KI = DCP / 8, KW = KI / NWB;
-    static_assert(KI % NWB == 0, "ingest items per wave");
-    float pv[KW][8];
-#pragma unroll
-    for (int kw = 0; kw < KW; ++kw)
-#pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const int c = 8 * (wave + NWB * kw) + t;
-        const bool ok = c < Cin;
-        const float x = planes[((size_t)b * Cin + (ok ? c : 0)) * 64 + lane];
-        pv[kw][t] = ok ? x : 0.0f;
-      }
-#pragma unroll
-    for (int kw = 0; kw < KW; ++kw) {
-      const int k = wave + NWB * kw;
-      *reinterpret_cast<uint4*>(smem + OFF_T + lane * 128 + ((k ^ swz128(lane)) << 4)) =
-          make_uint4(pack_bf16x2(pv[kw][0], pv[kw][1]), pack_bf16x2(pv[kw][2], pv[kw][3]),
-                     pack_bf16x2(pv[kw][4], pv[kw][5]), pack_bf16x2(pv[kw][6], pv[kw][7]));
-    }
-  }
-
-  // tower weight stream, read through a buffer resource: the lane's offsets
-  // (its own block, and block 4) are constant VGPRs, a step's byte offset is a
-  // scalar and a block's a literal, so the loads cost no vector address
-  // arithmetic.  K step i of the stream lives in ring slot i % NBUF, loaded
-  // NBUF - 1 steps ahead: a wave's K step is two or three MFMAs, so the ring is
-  // deep enough to cover a load from L2 or the Infinity Cache (int8 15 steps,
-  // bf16 10: measured best among the depths that tile two layers).
-  constexpr int NBUF = QUANT ? 15 : 10;
-  static_assert((2 * C::S) % NBUF == 0, "every block's first conv starts at ring slot 0");
-  const __amdgpu_buffer_rsrc_t twr = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<void*>(p.tower_w), (short)0, (int)(2 * p.blocks * C::LAYER_BYTES), 0x00020000);
-  const int tvoff = (mb0 * 64 + lane) * T::FB;
-  const int tvoffx = ((DNMB - 1) * 64 + lane) * T::FB;
-  // per-layer epilogue constants of conv index k (0 = stem): [bias F] floats, or
-  // [qbias F | qmul F] doubles, as thread-held 16-byte chunks loaded at the start
-  // of a layer and parked in LDS before its barrier
-  constexpr int KV = C::KSLOT / 16;                  // 16-byte chunks per slot
-  constexpr int KPL = (KV + NT - 1) / NT;            // per thread
-  auto load_consts = [&](int k, float4(&dst)[KPL]) {
-#pragma unroll
-    for (int t = 0; t < KPL; ++t) {
-      const int i = tid + NT * t;
-      const void* src;
-      if constexpr (QUANT)
-        src = i < DF / 2 ? p.qbias + (size_t)k * DF + 2 * i
-              : i < DF   ? p.qmul + (size_t)k * DF + 2 * (i - DF / 2)
-                         : p.qext + 2 * (size_t)k;
-      else src = p.bias + (size_t)k * DF + 4 * i;
-      dst[t] = i < KV ? *reinterpret_cast<const float4*>(src) : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-  };
-  auto store_consts = [&](int slot, const float4(&v)[KPL]) {
-    float4* dst = reinterpret_cast<float4*>(smem + C::OFF_K + slot * C::KSLOT);
-#pragma unroll
-    for (int t = 0; t < KPL; ++t)
-      if (tid + NT * t < KV) dst[tid + NT * t] = v[t];
-  };
-  // head constants, staged once: embedding row scale and bias, query and key biases
-  {
-    float* hc = reinterpret_cast<float*>(smem + C::OFF_HC);
-    for (int i = tid; i < AZ_DEP_EMB_ROWS; i += NT) {
-      hc[i] = p.emb_sc[i];
-      hc[AZ_DEP_EMB_ROWS + i] = p.emb_bc[i];
-    }
-    for (int i = tid; i < DD; i += NT) {
-      hc[2 * AZ_DEP_EMB_ROWS + i] = p.q_b[i];
-      hc[2 * AZ_DEP_EMB_ROWS + DD + i] = p.k_b[i];
-    }
-  }
-  {
-    float4 k0[KPL];
-    load_consts(1, k0);
-    store_consts(0, k0);
-  }
-
-  // ---- stem and tower of one wave.  XN >= 0: the wave also owns tile (4, XN).
-  // Fragment / accumulator set m < MBW is block mb0 + m (both tiles); set MBW,
-  // when present, is block 4 (tile XN only).  Every wave meets the same
-  // sequence of workgroup barriers.
-  // int8 layers without pooling move the epilogue of tile (4, n) from wave n to
-  // wave 2 + n (MV = n), which finishes its K loop earlier; the tile's
-  // accumulators go through LDS.
-  constexpr bool MOVE = QUANT;
-  auto trunk = [&](auto xn_c, auto mv_c) {
-    constexpr int XN = decltype(xn_c)::value;
-    constexpr int MV = decltype(mv_c)::value;      // tile (4, MV)'s moved epilogue (waves 2, 3)
-    constexpr int NAF = MBW + (XN >= 0 ? 1 : 0);   // weight fragments per K step
-    auto blk_of = [&](int m) { return m < MBW ? mb0 + m : DNMB - 1; };
-    auto n_lo = [](int m) constexpr { return m < MBW ? 0 : (XN >= 0 ? XN : MV); };
-    auto n_hi = [](int m) constexpr { return m < MBW ? NBW : (XN >= 0 ? XN : MV) + 1; };
-
-    // residual stream of the board (bf16 networks): h = hi + lo, hi = bf16(h) in
-    // the H buffer (the convolution operand), lo = bf16(h - hi) packed here, two
-    // per register: [set][half][run of 4 channels][2]
-    uint32_t rlo[QUANT ? 1 : NAF][QUANT ? 1 : NBW][QUANT ? 1 : 8];
-
-    frag_t A[NBUF][NAF];
-    auto load_step = [&](frag_t(&dst)[NAF], int soff) {
-#pragma unroll
-      for (int m = 0; m < MBW; ++m)
-        dst[m] = __builtin_bit_cast(frag_t, __builtin_amdgcn_raw_buffer_load_b128(twr, tvoff, soff + m * 64 * T::FB, 0));
-      if constexpr (NAF > MBW)
-        dst[MBW] = __builtin_bit_cast(frag_t, __builtin_amdgcn_raw_buffer_load_b128(twr, tvoffx, soff, 0));
-    };
-
-    // ---- stem: bf16 3x3 conv over 64 (padded) input channels, K = 576
-    {
-      constexpr int SSTEP = DNMB * 64 * 16;  // bytes per K step of the stem stream
-      const uint8_t* sw8 = static_cast<const uint8_t*>(p.stem_w) + (size_t)lane * 16;
-      f32x16 sacc[NAF][NBW];
-      // 36 K steps (tap = st / 4, 16 channels each): A fragments of step st in ring
-      // slot st % 12, loaded eleven steps ahead, the first ones before the ingest
-      // barrier; B fragments one step ahead
-      constexpr int SR = 12, NST = 9 * DCP / 16;
-      bf16x8 a[SR][NAF];
-      auto load_a = [&](int st) {
-#pragma unroll
-        for (int m = 0; m < NAF; ++m) a[st % SR][m] = g_frag<MK_BF16>(sw8 + st * SSTEP + blk_of(m) * 64 * 16);
-      };
-      auto load_b = [&](int st, bf16x8(&dst)[NBW]) {
-        const int tap = st / 4, cs = st % 4, dy = tap / 3 - 1, dx = tap % 3 - 1;
-#pragma unroll
-        for (int n = 0; n < NBW; ++n) {
-          const int j = n * 32 + l32, r = (j >> 3) + dy, c = (j & 7) + dx;
-          const bool ok = (unsigned)r < 8u && (unsigned)c < 8u;
-          const int src = r * 8 + c;
-          const int row = ok ? OFF_T + src * 128 : OFF_Z + ((src * 128) & 255);
-          dst[n] = *reinterpret_cast<const bf16x8*>(smem + row + (((2 * cs + lhi) ^ swz128(src)) << 4));
-        }
-      };
-#pragma unroll
-      for (int st = 0; st < SR - 1; ++st) load_a(st);
-      __syncthreads();  // the ingest's planes and constants are in LDS
-      bf16x8 bcur[NBW], bnext[NBW];
-      load_b(0, bcur);
-#pragma unroll
-      for (int st = 0; st < NST; ++st) {
-        if (st + SR - 1 < NST) load_a(st + SR - 1);
-        if (st + 1 < NST) load_b(st + 1, bnext);
-#pragma unroll
-        for (int m = 0; m < NAF; ++m)
-#pragma unroll
-          for (int n = n_lo(m); n < n_hi(m); ++n)
-            sacc[m][n] = mma_bf16(a[st % SR][m], bcur[n], st == 0 ? f32x16{} : sacc[m][n]);
-#pragma unroll
-        for (int n = 0; n < NBW; ++n) bcur[n] = bnext[n];
-      }
-      // the tower's first weight steps, in flight during the stem's epilogue
-      static_for<0, NBUF - 1>([&](auto i_c) {
-        constexpr int i = decltype(i_c)::value;
-        load_step(A[i], i * C::STEP_BYTES);
-      });
-      // epilogue: bias, activation (codes for int8), store in the tower format at OFF_H
-#pragma unroll
-      for (int m = 0; m < NAF; ++m)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int ch0 = blk_of(m) * 32 + 8 * q + 4 * lhi;
-          const float4 bb = *reinterpret_cast<const float4*>(p.bias + ch0);
-          double mq[4] = {}, bq[4] = {};
-          if constexpr (QUANT) {
-  #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              mq[r] = p.qmul[ch0 + r];
-              bq[r] = p.qbias[ch0 + r];
-            }
-          }
-#pragma unroll
-          for (int n = n_lo(m); n < n_hi(m); ++n) {
-            const int j = n * 32 + l32;
-            const f32x16& v = sacc[m][n];
-            if constexpr (!QUANT) {
-              const float y0 = act_fn(v[4 * q + 0] + bb.x, cap), y1 = act_fn(v[4 * q + 1] + bb.y, cap);
-              const float y2 = act_fn(v[4 * q + 2] + bb.z, cap), y3 = act_fn(v[4 * q + 3] + bb.w, cap);
-              rlo[m][n][2 * q + 0] = pack_bf16x2(y0 - bf16_round(y0), y1 - bf16_round(y1));
-              rlo[m][n][2 * q + 1] = pack_bf16x2(y2 - bf16_round(y2), y3 - bf16_round(y3));
-              *reinterpret_cast<uint2*>(smem + OFF_H + j * RB + (R::pos(ch0 >> 3, R::sw(j)) << 4) + 8 * lhi) =
-                  make_uint2(pack_bf16x2(y0, y1), pack_bf16x2(y2, y3));
-            } else {
-              // fp32 sum of the bf16 matrix instruction; rescale and rounding in float64
-              *reinterpret_cast<uint32_t*>(smem + OFF_H + j * RB + (R::pos(ch0 >> 4, R::sw(j)) << 4) + (ch0 & 15)) =
-                  pack_codes_d<MK>(__builtin_fma((double)v[4 * q + 0], mq[0], bq[0]),
-                                   __builtin_fma((double)v[4 * q + 1], mq[1], bq[1]),
-                                   __builtin_fma((double)v[4 * q + 2], mq[2], bq[2]),
-                                   __builtin_fma((double)v[4 * q + 3], mq[3], bq[3]), p.qhi[0]);
-            }
-          }
-        }
-    }
-    __syncthreads();
-
-    // ---- residual tower
-    {
-      constexpr int CPT = C::CPT;
-      acc_t c[MBW + 1][NBW];
-      const int nconv = 2 * p.blocks;
-
-      const int l32_ = l32, lhi_ = lhi;
-      auto conv = [&](auto second_c, auto pool_c, auto lb_c, int n_conv) {
-        constexpr bool SECOND = decltype(second_c)::value;
-        constexpr bool POOL = decltype(pool_c)::value;   // first conv of a pooling block
-        constexpr int LB = decltype(lb_c)::value;        // ring slot of the layer's first step
-        // lane coordinates, opaque to the compiler per layer, so that the layer's
-        // many lane-dependent addresses are computed in the layer instead of being
-        // hoisted out of the block loop and held (or spilled) across it
-        int l32 = l32_, lhi = lhi_;
-        asm volatile("" : "+v"(l32), "+v"(lhi));
-        const int wl = n_conv * (int)C::LAYER_BYTES;  // byte offset of the layer in the stream
-        const bool has_next = n_conv + 1 < nconv;
-        const int in_off = SECOND ? OFF_T : OFF_H;
-        const int out_off = SECOND ? OFF_H : OFF_T;
-        float* kslot = reinterpret_cast<float*>(smem + C::OFF_K + (n_conv & 1) * C::KSLOT);
-        // the next layer's epilogue constants, in flight during this layer
-        float4 kn[KPL];
-        if (has_next) load_consts(n_conv + 2, kn);
-        // a pooling layer's projection weights (waves 0 and 1: output 64 wave +
-        // lane, all 2g inputs as [i/4] float4s), in flight during the K loop
-        constexpr int NWP = POOL ? 2 * DG / 4 : 1;
-        float4 wpool[NWP];
-        if constexpr (POOL) {
-          const float4* wt = reinterpret_cast<const float4*>(p.pool_wt) +
-                             (size_t)(n_conv / 2 / p.pool_every) * (2 * DG / 4) * AZ_DEP_POOL_OPAD + 64 * (wave & 1) + lane;
-#pragma unroll
-          for (int i4 = 0; i4 < NWP; ++i4) wpool[i4] = wt[(size_t)i4 * AZ_DEP_POOL_OPAD];
-        }
-        // B fragments of one K step.  Channel step cs reads logical chunk
-        // lc = 2 cs + lhi of the tap's row, at chunk position (lc + rot) mod NC with
-        // rot the row's rotation: from a per-tap base b0 = row + 16 (lhi + rot) the
-        // address is b0 + 32 cs, except for the last steps, where lc + rot can pass
-        // the row's end and the base is chosen per lane once per tap.
-        constexpr int WRAP0 = (R::NC - 1 - R::RM) / 2;  // first step that can wrap
-        constexpr int NWRAP = CPT > WRAP0 ? CPT - WRAP0 : 0;
-        struct TapRows {
-          int b0[NBW];
-          int bw[NBW][NWRAP > 0 ? NWRAP : 1];
         };
-        TapRows row, nrow;
-        auto rows_for = [&](int tap, TapRows& tr) {
-          const int dy = tap / 3 - 1, dx = tap % 3 - 1;
-#pragma unroll
-          for (int n = 0; n < NBW; ++n) {
-            const int j = n * 32 + l32, r = (j >> 3) + dy, cc = (j & 7) + dx;
-            const bool ok = (unsigned)r < 8u && (unsigned)cc < 8u;
-            const int src = r * 8 + cc;
-            const int ra = in_off + src * RB, rz = OFF_Z + ((src * RB) & 255);
-            const int msk = -(int)ok;
-            const int x = lhi + R::sw(src);
-            tr.b0[n] = ((ra & msk) | (rz & ~msk)) + 16 * x;
-#pragma unroll
-            for (int k = 0; k < NWRAP; ++k)
-              tr.bw[n][k] = tr.b0[n] - (2 * (WRAP0 + k) + x >= R::NC ? 16 * R::NC : 0);
-          }
-        };
-        auto load_b = [&](const TapRows& tr, auto cs_c, frag_t(&dst)[NBW]) {
-          constexpr int cs = decltype(cs_c)::value;
-#pragma unroll
-          for (int n = 0; n < NBW; ++n) {
-            int base;
-            if constexpr (cs >= WRAP0) base = tr.bw[n][cs - WRAP0];
-            else base = tr.b0[n];
-            dst[n] = *reinterpret_cast<const frag_t*>(smem + base + 32 * cs);
-          }
-        };
-        frag_t bc[NBW], bn[NBW];
-        rows_for(0, row);
-        load_b(row, std::integral_constant<int, 0>{}, bc);
-
-        // one tap: CPT K steps; R0 = ring slot of its first step
-        auto tap_body = [&](auto r0_c, auto first_c, int tap) {
-          constexpr int R0 = decltype(r0_c)::value;
-          constexpr bool FIRST = decltype(first_c)::value;
-          rows_for(tap + 1, nrow);
-          static_for<0, CPT>([&](auto cs_c) {
-            constexpr int cs = decltype(cs_c)::value;
-            constexpr int cur = (R0 + cs) % NBUF;
-            {
-              // step tap*CPT + cs + NBUF-1 of this layer (of the next layer past its end;
-              // past the network's last layer this layer is re-read and never used)
-              const int gi = tap * CPT + cs + NBUF - 1;
-              load_step(A[(cur + NBUF - 1) % NBUF], wl + ((has_next || gi < C::S) ? gi * C::STEP_BYTES : 0));
-            }
-            if constexpr (cs + 1 < CPT) load_b(row, std::integral_constant<int, cs + 1>{}, bn);
-            else load_b(nrow, std::integral_constant<int, 0>{}, bn);
-#pragma unroll
-            for (int m = 0; m < NAF; ++m)
-#pragma unroll
-              for (int n = n_lo(m); n < n_hi(m); ++n)
-                c[m][n] = T::mma(A[cur][m], bc[n], (FIRST && cs == 0) ? acc_t{} : c[m][n]);
-#pragma unroll
-            for (int n = 0; n < NBW; ++n) bc[n] = bn[n];
-            // each MFMA followed by one of the next step's LDS reads, then by one of
-            // the prefetched step's weight loads
-            static_for<0, MBW * NBW + NAF - MBW>([&](auto i_c) {
-              constexpr int i = decltype(i_c)::value;
-              __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-              if constexpr (i < NBW) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-              if constexpr (i < NAF) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-            });
-          });
-          row = nrow;
-        };
-        constexpr int U = NBUF / gcd_c(CPT, NBUF), NIT = 8 / U, REM = 8 % U;
-        tap_body(std::integral_constant<int, LB>{}, std::true_type{}, 0);
-#pragma nounroll
-        for (int it = 0; it < NIT; ++it) {
-          static_for<0, U>([&](auto u_c) {
-            constexpr int u = decltype(u_c)::value;
-            tap_body(std::integral_constant<int, (LB + (1 + u) * CPT) % NBUF>{}, std::false_type{}, 1 + it * U + u);
-          });
-        }
-        static_for<0, REM>([&](auto u_c) {
-          constexpr int u = decltype(u_c)::value, t = 1 + NIT * U + u;
-          tap_body(std::integral_constant<int, (LB + t * CPT) % NBUF>{}, std::false_type{}, t);
-        });
-
-        // global pooling: pooled channels' board mean and maximum, projected to a
-        // context term that is folded into the regular channels' bias (in place in
-        // this layer's constant slot)
-        if constexpr (POOL) {
-          // (1) the pooled channels to LDS as [pooled channel][square] in the T
-          //     buffer (written by this layer's epilogue only afterwards); rows of
-          //     256 bytes with 16-byte chunks XOR-swizzled by the row.  int8: the
-          //     exact accumulators, activated in float64 in (2); bf16: act(acc + b1)
-          float* pt = reinterpret_cast<float*>(smem + OFF_T);
-          static_assert(DG * 64 * 4 <= C::BUF, "pooled activations fit in the T buffer");
-          static_for<0, NAF * 4>([&](auto k_c) {
-            constexpr int k = decltype(k_c)::value, m = k / 4, q = k % 4;
-            if (32 * blk_of(m) + 8 * q >= DFR) {
-              const int ch0 = 32 * blk_of(m) + 8 * q + 4 * lhi;
-              float4 bb = make_float4(0.f, 0.f, 0.f, 0.f);
-              if constexpr (!QUANT) bb = *reinterpret_cast<const float4*>(kslot + ch0);
-              const float bv[4] = {bb.x, bb.y, bb.z, bb.w};
-#pragma unroll
-              for (int r = 0; r < 4; ++r) {
-                const int pc = ch0 + r - DFR;
-#pragma unroll
-                for (int n = n_lo(m); n < n_hi(m); ++n) {
-                  const int sq = 32 * n + l32, idx = pc * 64 + (((sq >> 2) ^ (pc & 15)) << 2) + (sq & 3);
-                  if constexpr (QUANT) reinterpret_cast<int*>(pt)[idx] = (int)c[m][n][4 * q + r];
-                  else pt[idx] = med3(c[m][n][4 * q + r] + bv[r], 0.0f, cap);
-                }
-              }
-            }
-          });
-          wave_lds_sync();
-          // (2) wave w, lane l < g/4: board sum (fp64) and maximum of row
-          //     pc = g/4 w + l; g = [mean, max]
-          double* pg = reinterpret_cast<double*>(smem + C::OFF_PG);
-          static_assert(DG % 4 == 0, "pooled rows per wave");
-          if (lane < DG / 4) {
-            const int pc = (DG / 4) * wave + lane;
-            const double2 mx_sum = pool_row<QUANT>(p, pt, pc, n_conv);
-            pg[pc] = mx_sum.y * (1.0 / 64.0);
-            pg[DG + pc] = mx_sum.x;
-          }
-          wave_lds_sync();
-          // (3) c[o] = sum_i Wg[o][i] g[i] in fp64 (fp32 weights are exact): waves 0
-          //     and 1 take output 64 wave + lane with the prefetched weights
-          if (wave < 2) {
-            const int o = 64 * wave + lane;
-            double co = 0.0;
-#pragma unroll
-            for (int i4 = 0; i4 < NWP; ++i4) {
-              const float4 w = wpool[i4];
-              const double* gi = pg + 4 * i4;
-              co = __builtin_fma((double)w.x, gi[0], co);
-              co = __builtin_fma((double)w.y, gi[1], co);
-              co = __builtin_fma((double)w.z, gi[2], co);
-              co = __builtin_fma((double)w.w, gi[3], co);
-            }
-            // regular channel o's bias takes c[o] (int8: in code units, c[o] / a[n+1])
-            if (o < DFR) add_context<QUANT>(p, kslot, o, co, n_conv);
-          }
-          wave_lds_sync();
-        }
-
-        // epilogue: per run of 4 channels; LDS reads of constants (and residual
-        // codes) issued two runs ahead
-        float hi = 0.0f;
-        double rq = 0.0;
-        if constexpr (QUANT) {
-          const double* kd = reinterpret_cast<const double*>(kslot);
-          hi = (float)kd[2 * DF + 1];
-          rq = SECOND ? kd[2 * DF] : 0.0;
-        }
-        constexpr int EP_AHEAD = 2, EP_RING = EP_AHEAD + 1;
-        constexpr bool RCODE = QUANT && SECOND;   // residual codes, read in place
-        constexpr bool RHI = !QUANT && SECOND;    // residual hi parts, read in place
-        // int8 constants: qbias and qmul of the run's four channels, float64
-        struct KQ { double b[4], m[4]; };
-        float4 kb[QUANT ? 1 : EP_RING];
-        KQ kq[QUANT ? EP_RING : 1];
-        uint32_t rcode[RCODE ? EP_RING : 1][NBW];
-        uint2 rhi[RHI ? EP_RING : 1][NBW];
-        auto ep_addr = [&](int m, int q, int n) {
-          const int j = n * 32 + l32;
-          const int ch0 = blk_of(m) * 32 + 8 * q + 4 * lhi;
-          const int rowo = out_off + j * RB;
-          if constexpr (QUANT) return rowo + (R::pos(ch0 >> 4, R::sw(j)) << 4) + (ch0 & 15);
-          else return rowo + (R::pos(ch0 >> 3, R::sw(j)) << 4) + 8 * lhi;
-        };
-        auto ep_load = [&](auto k_c) {
+        static_for<0, EP_AHEAD>([&](auto k_c) { ep_load(k_c); });
+        static_for<0, NRUN>([&](auto k_c) {
           constexpr int k = decltype(k_c)::value, m = k / 4, q = k % 4, slot = k % EP_RING;
-          const int ch0 = blk_of(m) * 32 + 8 * q + 4 * lhi;
-          if constexpr (QUANT) {
-            const double* kd = reinterpret_cast<const double*>(kslot);
-  #pragma unroll
-            for (int r = 0; r < 4; r += 2) {
-              const double2 b2 = *reinterpret_cast<const double2*>(kd + ch0 + r);
-              const double2 m2 = *reinterpret_cast<const double2*>(kd + DF + ch0 + r);
-              kq[slot].b[r] = b2.x;
-              kq[slot].b[r + 1] = b2.y;
-              kq[slot].m[r] = m2.x;
-              kq[slot].m[r + 1] = m2.y;
-            }
+          if constexpr (k + EP_AHEAD < NRUN) ep_load(std::integral_constant<int, k + EP_AHEAD>{});
+          const int ch0 = ch_of(m, q);
+          if constexpr (m == 0) {
+#pragma unroll
+            for (int n = 0; n < NBK; ++n)
+              ep_run(q, kq[slot], c[n], run_addr(out_off, ch0, n), SECOND ? rin[SECOND ? slot : 0][SECOND ? n : 0] : rin_t{},
+                     rlo[QUANT ? 0 : n]);
           } else {
-            kb[slot] = *reinterpret_cast<const float4*>(kslot + ch0);
-          }
-          if constexpr (RCODE) {
 #pragma unroll
-            for (int n = n_lo(m); n < n_hi(m); ++n) rcode[slot][n] = *reinterpret_cast<const uint32_t*>(smem + ep_addr(m, q, n));
-          }
-          if constexpr (RHI) {
-#pragma unroll
-            for (int n = n_lo(m); n < n_hi(m); ++n) rhi[slot][n] = *reinterpret_cast<const uint2*>(smem + ep_addr(m, q, n));
-          }
-        };
-        // runs [K0, K1) (run k: set k / 4, channels 8 (k % 4) .. of the set's block)
-        auto epi_runs = [&](auto k0_c, auto k1_c) {
-        constexpr int K0 = decltype(k0_c)::value, K1 = decltype(k1_c)::value;
-        static_for<K0, (K0 + EP_AHEAD < K1 ? K0 + EP_AHEAD : K1)>([&](auto k_c) { ep_load(k_c); });
-        static_for<K0, K1>([&](auto k_c) {
-          constexpr int k = decltype(k_c)::value, m = k / 4, q = k % 4, slot = k % EP_RING;
-          if constexpr (k + EP_AHEAD < K1) ep_load(std::integral_constant<int, k + EP_AHEAD>{});
-#pragma unroll
-          for (int n = n_lo(m); n < n_hi(m); ++n) {
-            const int addr = ep_addr(m, q, n);
-            const acc_t& v = c[m][n];
-            if constexpr (!QUANT) {
-              const float4 bb = kb[slot];
-              float y0 = v[4 * q + 0] + bb.x, y1 = v[4 * q + 1] + bb.y;
-              float y2 = v[4 * q + 2] + bb.z, y3 = v[4 * q + 3] + bb.w;
-              if constexpr (SECOND) {
-                // block input h = hi + lo (exact in fp32)
-                const uint2 hv = rhi[slot][n];
-                const uint32_t l01 = rlo[m][n][2 * q], l23 = rlo[m][n][2 * q + 1];
-                y0 = act_fn(y0 + (__uint_as_float(hv.x << 16) + __uint_as_float(l01 << 16)), cap);
-                y1 = act_fn(y1 + (__uint_as_float(hv.x & 0xffff0000u) + __uint_as_float(l01 & 0xffff0000u)), cap);
-                y2 = act_fn(y2 + (__uint_as_float(hv.y << 16) + __uint_as_float(l23 << 16)), cap);
-                y3 = act_fn(y3 + (__uint_as_float(hv.y & 0xffff0000u) + __uint_as_float(l23 & 0xffff0000u)), cap);
-                rlo[m][n][2 * q + 0] = pack_bf16x2(y0 - bf16_round(y0), y1 - bf16_round(y1));
-                rlo[m][n][2 * q + 1] = pack_bf16x2(y2 - bf16_round(y2), y3 - bf16_round(y3));
-              } else {
-                y0 = act_fn(y0, cap);
-                y1 = act_fn(y1, cap);
-                y2 = act_fn(y2, cap);
-                y3 = act_fn(y3, cap);
-              }
-              *reinterpret_cast<uint2*>(smem + addr) = make_uint2(pack_bf16x2(y0, y1), pack_bf16x2(y2, y3));
-            } else {
-              // float64 requantisation: z = acc * qmul + qbias (+ residual code * qres)
-              const KQ& kk = kq[slot];
-              double z[4];
-  #pragma unroll
-              for (int r = 0; r < 4; ++r) z[r] = __builtin_fma((double)v[4 * q + r], kk.m[r], kk.b[r]);
-              if constexpr (SECOND) {
-                const uint32_t rc = rcode[slot][n];
-                z[0] = __builtin_fma(code_value_d<MK, 0>(rc), rq, z[0]);
-                z[1] = __builtin_fma(code_value_d<MK, 1>(rc), rq, z[1]);
-                z[2] = __builtin_fma(code_value_d<MK, 2>(rc), rq, z[2]);
-                z[3] = __builtin_fma(code_value_d<MK, 3>(rc), rq, z[3]);
-              }
-              *reinterpret_cast<uint32_t*>(smem + addr) = pack_codes_d<MK>(z[0], z[1], z[2], z[3], hi);
-            }
+            for (int n = 0; n < XB; ++n)
+              ep_run(q, kq[slot], cx[n], run_addr(out_off, ch0, xfirst + n),
+                     SECOND ? rin[SECOND ? slot : 0][SECOND ? n : 0] : rin_t{}, rlox[QUANT ? 0 : n]);
           }
         });
-        };
-        constexpr bool MOVED = MOVE && !POOL;   // this layer moves tile (4, n)'s epilogue
-        if constexpr (MOVED) {
-          uint32_t* xa = reinterpret_cast<uint32_t*>(smem + C::OFF_Q4);   // [tile][16 values][64 lanes]
-          if constexpr (XN >= 0) {
-#pragma unroll
-            for (int v = 0; v < 16; ++v) xa[(XN * 16 + v) * 64 + lane] = (uint32_t)c[MBW][XN][v];
-            wave_lds_sync();
-            epi_runs(std::integral_constant<int, 0>{}, std::integral_constant<int, MBW * 4>{});
-          } else {
-            epi_runs(std::integral_constant<int, 0>{}, std::integral_constant<int, MBW * 4>{});
-            wave_lds_sync();
-#pragma unroll
-            for (int v = 0; v < 16; ++v) c[MBW][MV][v] = (int)xa[(MV * 16 + v) * 64 + lane];
-            epi_runs(std::integral_constant<int, MBW * 4>{}, std::integral_constant<int, MBW * 4 + 4>{});
-          }
-        } else {
-          epi_runs(std::integral_constant<int, 0>{}, std::integral_constant<int, NAF * 4>{});
-        }
         if (has_next) store_consts((n_conv + 1) & 1, kn);
         __syncthreads();
       };
 
       for (int blk = 0; blk < p.blocks; ++blk) {
         const bool pool = p.pool_every > 0 && blk % p.pool_every == p.pool_every - 1;
-        if (pool) conv(std::false_type{}, std::true_type{}, std::integral_constant<int, 0>{}, 2 * blk);
-        else conv(std::false_type{}, std::false_type{}, std::integral_constant<int, 0>{}, 2 * blk);
-        conv(std::true_type{}, std::false_type{}, std::integral_constant<int, C::S % NBUF>{}, 2 * blk + 1);
+        conv(std::false_type{}, 2 * blk, pool);
+        conv(std::true_type{}, 2 * blk + 1, pool);
       }
     }
 
-    // ---- heads input (bf16 networks): the low part h - bf16(h) of the fp32
-    // residual as bf16 rows [square][F] at OFF_X, H holding bf16(h); int8
-    // networks read the final codes from H and convert them in registers
+    // ---- heads input (bf16 networks): the low part h - bf16(h) of the residual in
+    // the tower's layout at OFF_X, H holding bf16(h); int8 networks read the final
+    // codes from H and convert them in registers
     if constexpr (!QUANT) {
-      using RX = Rot<C::RBX>;
 #pragma unroll
-      for (int m = 0; m < NAF; ++m)
+      for (int q = 0; q < 4; ++q) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int ch0 = blk_of(m) * 32 + 8 * q + 4 * lhi;
+        for (int n = 0; n < NBK; ++n)
+          *reinterpret_cast<uint2*>(smem + run_addr(C::OFF_X, ch_of(0, q), n)) = make_uint2(rlo[n][2 * q], rlo[n][2 * q + 1]);
 #pragma unroll
-          for (int n = n_lo(m); n < n_hi(m); ++n) {
-            const int j = n * 32 + l32;
-            *reinterpret_cast<uint2*>(smem + C::OFF_X + j * C::RBX + (RX::pos(ch0 >> 3, RX::sw(j)) << 4) + 8 * lhi) =
-                make_uint2(rlo[m][n][2 * q], rlo[m][n][2 * q + 1]);
-          }
-        }
+        for (int k = 0; k < XB; ++k)
+          *reinterpret_cast<uint2*>(smem + run_addr(C::OFF_X, ch_of(1, q), xfirst + k)) =
+              make_uint2(rlox[k][2 * q], rlox[k][2 * q + 1]);
+      }
     }
   };
-  if (wave == 0) trunk(std::integral_constant<int, 0>{}, std::integral_constant<int, -1>{});
-  else if (wave == 1) trunk(std::integral_constant<int, 1>{}, std::integral_constant<int, -1>{});
-  else if (wave == 2) trunk(std::integral_constant<int, -1>{}, std::integral_constant<int, MOVE ? 0 : -1>{});
-  else trunk(std::integral_constant<int, -1>{}, std::integral_constant<int, MOVE ? 1 : -1>{});
+  using std::integral_constant;
+  if constexpr (BPG > 1) {
+    trunk(integral_constant<int, NBK / NWV>{}, integral_constant<int, 0>{});
+  } else {
+    if (wave == 0) trunk(integral_constant<int, 1>{}, integral_constant<int, 0>{});
+    else if (wave == 1) trunk(integral_constant<int, 1>{}, integral_constant<int, 1>{});
+    else trunk(integral_constant<int, 0>{}, integral_constant<int, 0>{});
+  }
   __syncthreads();
-  // ---- heads, shared by the four waves
-  dep_heads4<MK>(p, smem, legal, policy, value, wdl, b, wave, lane);
+  // ---- heads: one board shared by the four waves, or a wave per board
+  if constexpr (BPG == 1) {
+    dep_heads4<MK>(p, smem, legal, policy, value, wdl, b0, wave, lane);
+  } else {
+    const int bd = wave % BPG;  // waves past the boards only meet the barrier
+    dep_heads<MK, BPG>(p, smem, legal, policy, value, wdl, b0 + bd < B ? b0 + bd : B - 1, bd,
+                       wave < BPG && b0 + bd < B, lane);
+  }
 }
 
+template <int MK, int BPG, int NBUF, int SR>
+hipError_t launch_dep(const AzDevNet& n, const float* planes, const uint8_t* legal, int B, float* policy, float* value,
+                      float* wdl, hipStream_t s) {
+  (void)hipGetLastError();
+  if (n.filters != DF || B <= 0) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((az_dep_kernel<MK, BPG, NBUF, SR>), dim3((B + BPG - 1) / BPG), dim3(256), 0, s, n, planes, legal, B,
+                     policy, value, wdl);
+  return hipGetLastError();
+}
 
 }  // namespace

@@ -94,11 +94,11 @@ struct AzDevNet {
 hipError_t az_launch_mfma(int dtype, int tiling, const AzDevNet& net, const float* planes,
                           const uint8_t* legal, int B, float* policy, float* value,
                           hipStream_t stream);
-// Deployed network (F = 160) in int8 or bf16; wdl may be NULL.  tiling: 1 = one
-// wave per board, 2 = four waves per board.
-hipError_t az_launch_deployed_int8(const AzDevNet& net, int tiling, const float* planes, const uint8_t* legal,
+// Deployed network (F = 160) in int8 or bf16; wdl may be NULL.  boards per
+// workgroup: 1, 2 or (int8) 0 for a wave per board.
+hipError_t az_launch_deployed_int8(const AzDevNet& net, int boards, const float* planes, const uint8_t* legal,
                                    int B, float* policy, float* value, float* wdl, hipStream_t stream);
-hipError_t az_launch_deployed_bf16(const AzDevNet& net, int tiling, const float* planes, const uint8_t* legal,
+hipError_t az_launch_deployed_bf16(const AzDevNet& net, int boards, const float* planes, const uint8_t* legal,
                                    int B, float* policy, float* value, float* wdl, hipStream_t stream);
 hipError_t az_launch_f32(const AzDevNet& net, const float* planes, const uint8_t* legal, int B,
                          float* policy, float* value, hipStream_t stream);

@@ -14,8 +14,8 @@
 // construction.  Order: stem (bf16), then the 2*blocks residual convs, then
 // the head: 96 rows (policy planes, value 1x1 conv row, zero rows), K = F.
 //
-// The deployed network (from-to policy, WDL value, global pooling) orders its K
-// steps tap by tap (k = tap * C' + c), pads the stem to 64 input channels, packs the second convolution of a pooling block
+// The deployed network (from-to policy, WDL value, global pooling) pads the stem to
+// 64 input channels, packs the second convolution of a pooling block
 // ([F][Fr][3][3]) with zero weights for input channels Fr..F-1, and packs its
 // heads as described in az_dep_kernel.h.
 #include "../../include/az.h"
@@ -247,8 +247,8 @@ float e4m3_value(uint8_t c) {
 enum Kind { K_BF16 = 0, K_I8 = 1, K_F8 = 2 };
 
 // Packs a 3x3 conv W[F][Cin][3][3] (padded to Cp input channels) into A fragments,
-// tap by tap, or (rows) with the K steps ordered (dx, channel step, dy).
-void pack_conv(const float* W, const float* wscale, int F, int Cin, int Cp, Kind kind, bool rows,
+// K steps ordered (dx, channel step, dy).
+void pack_conv(const float* W, const float* wscale, int F, int Cin, int Cp, Kind kind,
                std::vector<uint8_t>& out) {
   const int KS = kind == K_BF16 ? 16 : kind == K_I8 ? 32 : 64;
   const int es = kind == K_BF16 ? 2 : 1;
@@ -258,8 +258,7 @@ void pack_conv(const float* W, const float* wscale, int F, int Cin, int Cp, Kind
   uint8_t* o = out.data() + base;
   const int cpt = Cp / KS;  // channel steps of a tap
   for (int s = 0; s < S; ++s) {
-    const int tap = rows ? 3 * (s % 3) + s / (3 * cpt) : s / cpt;
-    const int cs = rows ? s / 3 % cpt : s % cpt;
+    const int tap = 3 * (s % 3) + s / (3 * cpt), cs = s / 3 % cpt;
     for (int mb = 0; mb < nMB; ++mb)
       for (int l = 0; l < 64; ++l) {
         const int ch = mb * 32 + l % 32;
@@ -395,17 +394,25 @@ std::vector<uint32_t> fromto_actions() {
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Deployed network: the tiling with the shorter estimated time, rounds x time
-// per round.  A round is one board per compute unit with four waves per board,
-// and four (int8) or three (bf16, LDS-bound) boards per compute unit with one
-// wave per board; a round of the latter takes 2.5x (int8: ~370 against ~150 us)
-// or 2.8x (bf16: ~630 against ~225 us) as long as one of the former (14x160 on
-// MI355X).
+// Deployed network.  The tiling (az_net_tiling_for): 2 while the batch has at most
+// two boards per compute unit, 1 beyond it, and for bf16 2 again past three.
 int choose_dep_tiling(const az_net* n, int B) {
   const bool i8 = n->dtype == AZ_INT8;
   const long per1 = (long)n->cus * (i8 ? 4 : 3), per2 = n->cus;
   const long r1 = (B + per1 - 1) / per1, r2 = (B + per2 - 1) / per2;
   return r2 * 10 < r1 * (i8 ? 25 : 28) ? 2 : 1;
+}
+
+// Boards per workgroup of the deployed network's kernel (0: a wave per board).
+// Measured on 14x160 with 256 compute units (us; one / two boards per workgroup /
+// a wave per board): int8 256 boards 143 / 200 / 337, 333 boards 297 / 200 / 337, 512
+// boards 298 / 228 / 338, 600 boards - / 418 / 338, 1,024 boards 592 / 424 / 365; bf16
+// 256 boards 214 / 290 / -, 333 boards 427 / 293 / -, 1,024 boards 888 / 670 / -.
+int dep_boards(const az_net* n, int tiling, int B) {
+  const bool i8 = n->dtype == AZ_INT8;
+  if (tiling == 1) return i8 ? 0 : 2;
+  if (B <= n->cus) return 1;
+  return !i8 || B <= 2 * n->cus ? 2 : 0;
 }
 
 int choose_tiling(const az_net* n, int B) {
@@ -585,12 +592,12 @@ int az_net_load(const az_layer_spec* spec_in, const float* weights, size_t n_wei
       memcpy(hw.data() + (size_t)P * F, v.val_w, (size_t)F * sizeof(float));
       pack_split(P + 1, F, (F + 31) / 32, [&](int row, int k, int) { return hw[(size_t)row * F + k]; }, 1, head);
     } else {
-      pack_conv(v.stem_w, nullptr, F, Cin, dep ? AZ_DEP_MAX_IN_PLANES : 32, K_BF16, !dep, stem);
+      pack_conv(v.stem_w, nullptr, F, Cin, dep ? AZ_DEP_MAX_IN_PLANES : 32, K_BF16, stem);
       const Kind kind = dtype == AZ_BF16 ? K_BF16 : dtype == AZ_INT8 ? K_I8 : K_F8;
       for (int n = 0; n < 2 * NB; ++n) {
         // the second convolution of a pooling block reads the Fr regular channels
         const int cin = (n % 2 == 1 && is_pool_block(s, n / 2)) ? Fr : F;
-        pack_conv(v.w[n], quant ? w_scales + (size_t)n * F : nullptr, F, cin, F, kind, !dep, tower);
+        pack_conv(v.w[n], quant ? w_scales + (size_t)n * F : nullptr, F, cin, F, kind, tower);
       }
       if (!dep) pack_head(v, F, P, head);
       if (quant) {
@@ -800,7 +807,7 @@ int az_eval_batch_wdl(az_net* net, const float* planes, const uint8_t* legal, in
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (dep)
     e = (net->dtype == AZ_INT8 ? az_launch_deployed_int8 : az_launch_deployed_bf16)(
-        net->dn, choose_tiling(net, B), planes, legal, B, policy, value, wdl, s);
+        net->dn, dep_boards(net, choose_tiling(net, B), B), planes, legal, B, policy, value, wdl, s);
   else if (net->dtype == AZ_F32)
     e = az_launch_f32(net->dn, planes, legal, B, policy, value, s);
   else

@@ -224,6 +224,28 @@ def test_deployed_tilings_agree_bitwise(dtype):
         assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("dtype", ["int8", "bf16"])
+def test_deployed_board_counts(dtype):
+    # tiling 2 takes one board per workgroup up to a board per compute unit, then
+    # two, then (int8) a wave per board: around each step, with pooling blocks and an
+    # odd last workgroup, every row equals the one tiling 1 gives, and rows at the
+    # steps the oracle's
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    shape = _shape(2)
+    blob = azgen.make_weights(shape, 1066, alpha_fold=True, bf16=True)
+    ws, acs = _scales(shape, blob) if dtype == "int8" else (None, None)
+    planes, legal = _inputs(shape, 2 * cus + 3, 2266)
+    for B in (cus, cus + 1, 2 * cus - 1, 2 * cus + 3):
+        two = gpu_eval(shape, blob, dtype, planes[:B], legal[:B], ws, acs, tiling=2)
+        one = gpu_eval(shape, blob, dtype, planes[:B], legal[:B], ws, acs, tiling=1)
+        for a, b in zip(two, one):
+            assert np.array_equal(a, b)
+        rows = np.array([0, 1, 2, 3, B // 2, B - 2, B - 1])
+        ref = _oracle_rows(shape, blob, dtype, planes[rows], legal[rows], ws, acs)
+        _check(tuple(x[rows] for x in two), ref, legal[rows], dtype)
+
+
 def test_deployed_rows_do_not_depend_on_the_batch():
     shape = _shape(2)
     blob = azgen.make_weights(shape, 1006, alpha_fold=True, bf16=True)
