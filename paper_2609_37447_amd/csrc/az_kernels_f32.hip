@@ -20,7 +20,9 @@
 // the LDS fragments of one horizontal tap and channel step serve all three
 // vertical taps (block b's neighbour rows are block b +- 1).  A wave owns MB
 // channel blocks x NB square blocks, chosen so that one pass covers the layer:
-// 1 x 1 up to 32 filters, 1 x 2 up to 64, 1 x 4 up to 128, 2 x 4 up to 256.
+// 1 x 1 up to 16 filters, 1 x 2 up to 64, 1 x 4 up to 128, 2 x 4 up to 256 (32
+// filters: 1 x 1 20.7 us, 1 x 2 19.6 us; 64: 1 x 2 33 us, 1 x 4 36 us: the waves that
+// share a channel block each stream its weights through the L1).
 //
 // LDS holds one activation buffer: [square slot][part h, m, l][channel].  Slots
 // are 9 to a row with zero rows above and below the board and one zero column
@@ -218,6 +220,21 @@ __global__ __launch_bounds__(NT) void az_net_f32_kernel(AzDevNet p, const float*
     }
     __syncthreads();
   };
+  // the heads' first weight step, in flight during the tower where the registers
+  // allow
+  constexpr bool EARLY = MB == 1 && NB <= 2;
+  const int RBK = (P + 16) / 16, hrb0 = w >> 2;
+  const uint8_t* hw = static_cast<const uint8_t*>(p.head_w) + lane * 16;
+  Split ha[3];
+  auto load_head = [&](int cs) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const int rb = hrb0 + 2 * i < RBK ? hrb0 + 2 * i : RBK - 1;
+      const uint8_t* a = hw + (size_t)(cs * RBK + rb) * 3 * 1024;
+      ha[i] = Split{frag_at(a), frag_at(a + 1024), frag_at(a + 2048)};
+    }
+  };
+  if constexpr (EARLY) load_head(0);
   const uint8_t* tw = static_cast<const uint8_t*>(p.tower_w);
   const size_t layer = (size_t)3 * CP * group;
   conv(sw, 1, tw, p.bias, false, true);
@@ -253,20 +270,17 @@ __global__ __launch_bounds__(NT) void az_net_f32_kernel(AzDevNet p, const float*
   for (int s = 0; s < 16; ++s) f1[s] = reinterpret_cast<const float4*>(p.fc1_t)[(size_t)s * H + (unit ? tid : 0)];
   const float f1b = p.fc1_b[unit ? tid : 0], f2 = unit ? p.fc2_w[tid] : 0.0f;
   {
-    const int RBK = (P + 16) / 16, nb = w & 3, rb0 = w >> 2;
-    const uint8_t* hw = static_cast<const uint8_t*>(p.head_w) + lane * 16;
+    const int nb = w & 3, rb0 = hrb0;
     const uint8_t* q = sm + ((nb + 4 * hi4 + 1) * 9 + col + 1) * CS + kq * 16;
     f32x4 acc[3], sml[3];
 #pragma unroll
     for (int i = 0; i < 3; ++i) acc[i] = sml[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (!EARLY) load_head(0);
     for (int cs = 0; cs < CP; ++cs) {
       const Split x = {frag_at(q + cs * 64), frag_at(q + cs * 64 + RB), frag_at(q + cs * 64 + 2 * RB)};
 #pragma unroll
-      for (int i = 0; i < 3; ++i) {
-        const int rb = rb0 + 2 * i < RBK ? rb0 + 2 * i : RBK - 1;
-        const uint8_t* a = hw + (size_t)(cs * RBK + rb) * 3 * 1024;
-        mma_split(Split{frag_at(a), frag_at(a + 1024), frag_at(a + 2048)}, x, acc[i], sml[i]);
-      }
+      for (int i = 0; i < 3; ++i) mma_split(ha[i], x, acc[i], sml[i]);
+      load_head(cs + 1 < CP ? cs + 1 : cs);
     }
     __syncthreads();
     float* L = reinterpret_cast<float*>(sm);
@@ -352,6 +366,6 @@ hipError_t az_launch_f32(const AzDevNet& n, const float* planes, const uint8_t* 
   const int M16 = (n.filters + 15) / 16;  // 16-channel blocks: eight waves cover the layer's blocks once
   if (M16 > 8) return launch<2, 4>(n, planes, legal, B, policy, value, s);
   if (M16 > 4) return launch<1, 4>(n, planes, legal, B, policy, value, s);
-  if (M16 > 2) return launch<1, 2>(n, planes, legal, B, policy, value, s);
+  if (M16 > 1) return launch<1, 2>(n, planes, legal, B, policy, value, s);
   return launch<1, 1>(n, planes, legal, B, policy, value, s);
 }

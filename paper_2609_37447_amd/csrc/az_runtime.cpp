@@ -280,41 +280,66 @@ void pack_conv(const float* W, const float* wscale, int F, int Cin, int Cp, Kind
   }
 }
 
-// fp32 kernel: A fragments of a matrix of `rows` output channels and `chans` input
-// channels (padded with zeros to 16 rows and 32 channels) for each of `taps`
-// matrices of a channel step: fragment (channel step, tap, row block, part), lane
-// l holds part (bf16 h, m or l of w = h + m + l) of w(row 16 mb + l%16, channel
-// 32 cs + 8 (l/16) + t, tap), t = 0..7.
-template <class W>
-void pack_split(int rows, int chans, int steps, W w, int taps, std::vector<uint8_t>& out) {
-  const int M16 = (rows + 15) / 16;
-  const size_t base = out.size();
-  out.resize(base + (size_t)steps * taps * M16 * 3 * 1024);
-  uint8_t* o = out.data() + base;
-  for (int cs = 0; cs < steps; ++cs)
-    for (int tap = 0; tap < taps; ++tap)
-      for (int mb = 0; mb < M16; ++mb, o += 3 * 1024)
-        for (int l = 0; l < 64; ++l)
-          for (int t = 0; t < 8; ++t) {
-            const int row = mb * 16 + l % 16, c = cs * 32 + 8 * (l / 16) + t;
-            float x = row < rows && c < chans ? w(row, c, tap) : 0.0f;
-            for (int part = 0; part < 3; ++part) {
-              const uint16_t h = bf16_rne(x);
-              const uint32_t u = (uint32_t)h << 16;
-              float f;
-              memcpy(&f, &u, 4);
-              memcpy(o + part * 1024 + l * 16 + 2 * t, &h, 2);
-              x = isfinite(f) ? x - f : 0.0f;
-            }
-          }
+// The bf16 parts h, m, l of an fp32 weight w = h + m + l; a part of a non-finite
+// value is the value itself, the others zero.
+void split3(float x, uint32_t* parts) {
+  for (int i = 0; i < 3; ++i) {
+    const uint16_t h = bf16_rne(x);
+    const uint32_t u = (uint32_t)h << 16;
+    float f;
+    memcpy(&f, &u, 4);
+    parts[i] = h;
+    x = isfinite(f) ? x - f : 0.0f;
+  }
 }
 
-// A 3x3 conv W[F][C][3][3] for the fp32 kernel, groups ordered (dx, channel step),
-// the three dy of a group in order.
-void pack_conv_f32(const float* W, int F, int C, std::vector<uint8_t>& out) {
-  for (int dx = 0; dx < 3; ++dx)
-    pack_split(F, C, (C + 31) / 32, [&](int row, int c, int dy) { return W[((size_t)row * C + c) * 9 + 3 * dy + dx]; }, 3,
-               out);
+// fp32 kernel: A fragments of W[rows][chans][taps] (taps = 9: a 3x3 convolution, its
+// fragments ordered (dx, 32-channel step, dy); taps = 1), rows padded with zeros to
+// 16 and channels to 32: fragment (step, row block, part), lane l holds part (bf16
+// h, m or l of w = h + m + l) of rows 16 mb + l%16, channels 32 cs + 8 (l/16) + t.
+template <int TAPS>
+void pack_split(const float* W, int rows, int chans, std::vector<uint8_t>& out) {
+  const int M16 = (rows + 15) / 16, CP = (chans + 31) / 32;
+  const size_t base = out.size();
+  out.resize(base + (size_t)CP * TAPS * M16 * 3 * 1024);  // padding stays zero
+  uint8_t* o = out.data() + base;
+  constexpr int N = 8 * TAPS;  // a lane's eight channels, every tap
+  for (int row = 0; row < rows; ++row)
+    for (int c0 = 0; c0 < chans; c0 += 8) {
+      const int n = (chans - c0 < 8 ? chans - c0 : 8) * TAPS;
+      uint32_t u[N] = {}, part[3][N];
+      memcpy(u, W + ((size_t)row * chans + c0) * TAPS, n * sizeof(float));
+      uint32_t big = 0;  // a value that is not finite, or not once rounded
+      for (int i = 0; i < N; ++i) big |= (u[i] & 0x7fffffffu) >= 0x7f7f8000u;
+      if (big) {
+        for (int i = 0; i < N; ++i) {
+          float f;
+          uint32_t q[3];
+          memcpy(&f, &u[i], 4);
+          split3(f, q);
+          for (int k = 0; k < 3; ++k) part[k][i] = q[k];
+        }
+      } else {
+        for (int k = 0; k < 3; ++k)
+          for (int i = 0; i < N; ++i) {
+            const uint32_t r = (u[i] + 0x7fffu + ((u[i] >> 16) & 1u)) & 0xffff0000u;
+            float f, h;
+            memcpy(&f, &u[i], 4);
+            memcpy(&h, &r, 4);
+            f -= h;
+            memcpy(&u[i], &f, 4);
+            part[k][i] = r >> 16;
+          }
+      }
+      for (int tap = 0; tap < TAPS; ++tap) {
+        const int step = TAPS == 1 ? c0 / 32 : (tap % 3 * CP + c0 / 32) * 3 + tap / 3;
+        for (int k = 0; k < 3; ++k) {
+          uint16_t v[8];
+          for (int t = 0; t < 8; ++t) v[t] = (uint16_t)part[k][t * TAPS + tap];
+          memcpy(o + (((size_t)step * M16 + row / 16) * 3 + k) * 1024 + (row % 16 + 16 * (c0 % 32 / 8)) * 16, v, 16);
+        }
+      }
+    }
 }
 
 void pack_head(const BlobView& v, int F, int P, std::vector<uint8_t>& out) {
@@ -584,13 +609,16 @@ int az_net_load(const az_layer_spec* spec_in, const float* weights, size_t n_wei
         for (int c = 0; c < 64; ++c) fc1t[((size_t)(c / 4) * H + k) * 4 + (c % 4)] = v.fc1_w[(size_t)k * 64 + c];
     }
     if (dtype == AZ_F32) {
-      pack_conv_f32(v.stem_w, F, Cin, stem);
-      for (int n = 0; n < 2 * NB; ++n) pack_conv_f32(v.w[n], F, F, tower);
+      const int M16 = (F + 15) / 16;
+      stem.reserve((size_t)9 * M16 * 3 * 1024);
+      tower.reserve((size_t)2 * NB * 9 * ((F + 31) / 32) * M16 * 3 * 1024);
+      pack_split<9>(v.stem_w, F, Cin, stem);
+      for (int n = 0; n < 2 * NB; ++n) pack_split<9>(v.w[n], F, F, tower);
       // heads: P policy rows, then the value 1x1 conv's
       std::vector<float> hw((size_t)(P + 1) * F);
       memcpy(hw.data(), v.pol_w, (size_t)P * F * sizeof(float));
       memcpy(hw.data() + (size_t)P * F, v.val_w, (size_t)F * sizeof(float));
-      pack_split(P + 1, F, (F + 31) / 32, [&](int row, int k, int) { return hw[(size_t)row * F + k]; }, 1, head);
+      pack_split<1>(hw.data(), P + 1, F, head);
     } else {
       pack_conv(v.stem_w, nullptr, F, Cin, dep ? AZ_DEP_MAX_IN_PLANES : 32, K_BF16, stem);
       const Kind kind = dtype == AZ_BF16 ? K_BF16 : dtype == AZ_INT8 ? K_I8 : K_F8;
