@@ -71,18 +71,18 @@ def kernel_sha(shape, dtype):
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
 # (workload, tiling, batch): (kernel_sha, FETCH_SIZE KiB, WRITE_SIZE KiB, MFMA busy fraction)
 COUNTERS = {
-    ("net20x128_int8_b1024", 1, 1024): ("7f52e69d56ea062db334372d81332f33ea5f60b0334a17c53cccb4fe8b263aa2", 29227.8, 18696.0, 0.5293),
-    ("net20x128_int8_b1024", 3, 1024): ("7f52e69d56ea062db334372d81332f33ea5f60b0334a17c53cccb4fe8b263aa2", 35898.7, 18704.0, 0.5926),
-    ("net20x128_int8_b1024", 2, 64): ("7f52e69d56ea062db334372d81332f33ea5f60b0334a17c53cccb4fe8b263aa2", 24520.8, 1426.0, 0.0997),
-    ("net20x128_bf16_b1024", 1, 1024): ("7f52e69d56ea062db334372d81332f33ea5f60b0334a17c53cccb4fe8b263aa2", 52089.3, 18696.0, 0.6570),
-    ("net20x128_bf16_b256", 2, 256): ("7f52e69d56ea062db334372d81332f33ea5f60b0334a17c53cccb4fe8b263aa2", 48114.3, 4680.0, 0.5021),
-    ("net20x128_bf16_b32", 2, 32): ("7f52e69d56ea062db334372d81332f33ea5f60b0334a17c53cccb4fe8b263aa2", 47036.3, 585.0, 0.0642),
-    ("net20x128_fp8_b1024", 1, 1024): ("7f52e69d56ea062db334372d81332f33ea5f60b0334a17c53cccb4fe8b263aa2", 29304.8, 18696.0, 0.4522),
-    ("net24x256_bf16_b1024", 1, 1024): ("7f52e69d56ea062db334372d81332f33ea5f60b0334a17c53cccb4fe8b263aa2", 449866.8, 18704.0, 0.7632),
-    ("deployed14x160_int8_b1024", 1, 1024): ("5c99920884a7ae6b6f4b20e9d3a337117dccd2719057c9c6ce14ade7bafdd416", 36532.0, 7552.0, 0.4958),
-    ("deployed14x160_int8_b1024", 2, 64): ("5c99920884a7ae6b6f4b20e9d3a337117dccd2719057c9c6ce14ade7bafdd416", 29637.4, 472.0, 0.0743),
-    ("deployed14x160_bf16_b1024", 2, 1024): ("5c99920884a7ae6b6f4b20e9d3a337117dccd2719057c9c6ce14ade7bafdd416", 222194.4, 7552.0, 0.4100),
-    ("tiny_2x32_f32_b16", 0, 16): ("71a6c293790d7c1ed568fe2a55efb4c240b4ffe70594008f8c4af0194bf047ae", 1010.5, 292.5, 0.0000),
+    ("net20x128_int8_b1024", 1, 1024): ("f3d1ea1427b3ea1e798d96c1f19dadedeb5c17cff4c87c38eae7b0ff52a63e09", 29184.3, 18696.0, 0.5860),
+    ("net20x128_int8_b1024", 3, 1024): ("f3d1ea1427b3ea1e798d96c1f19dadedeb5c17cff4c87c38eae7b0ff52a63e09", 44332.1, 18704.0, 0.6655),
+    ("net20x128_int8_b1024", 2, 64): ("f3d1ea1427b3ea1e798d96c1f19dadedeb5c17cff4c87c38eae7b0ff52a63e09", 24370.8, 1170.0, 0.1051),
+    ("net20x128_bf16_b1024", 1, 1024): ("f3d1ea1427b3ea1e798d96c1f19dadedeb5c17cff4c87c38eae7b0ff52a63e09", 52070.3, 18696.0, 0.7210),
+    ("net20x128_bf16_b256", 2, 256): ("f3d1ea1427b3ea1e798d96c1f19dadedeb5c17cff4c87c38eae7b0ff52a63e09", 48110.3, 4680.0, 0.5974),
+    ("net20x128_bf16_b32", 2, 32): ("f3d1ea1427b3ea1e798d96c1f19dadedeb5c17cff4c87c38eae7b0ff52a63e09", 47032.3, 585.0, 0.0704),
+    ("net20x128_fp8_b1024", 1, 1024): ("f3d1ea1427b3ea1e798d96c1f19dadedeb5c17cff4c87c38eae7b0ff52a63e09", 29243.8, 18696.0, 0.4719),
+    ("net24x256_bf16_b1024", 1, 1024): ("f3d1ea1427b3ea1e798d96c1f19dadedeb5c17cff4c87c38eae7b0ff52a63e09", 450562.8, 18704.1, 0.8273),
+    ("deployed14x160_int8_b1024", 1, 1024): ("fc736842338dfe2064cd505dac3abeef8a7968170061d8a6636ae6df55049899", 35423.5, 7552.0, 0.4916),
+    ("deployed14x160_int8_b1024", 2, 64): ("fc736842338dfe2064cd505dac3abeef8a7968170061d8a6636ae6df55049899", 29223.9, 472.0, 0.0732),
+    ("deployed14x160_bf16_b1024", 2, 1024): ("fc736842338dfe2064cd505dac3abeef8a7968170061d8a6636ae6df55049899", 114946.9, 7536.0, 0.5637),
+    ("tiny_2x32_f32_b16", 0, 16): ("1aa299be26c797c412efab26d28cfe7012f75cfb22005dbb3afff0d58b7a026b", 1416.0, 292.5, 0.0078),
 }
 
 # MI355X published dense peaks (FLOP/s) at 2.4 GHz, 256 CUs.
