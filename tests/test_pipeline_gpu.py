@@ -291,3 +291,52 @@ def test_native_driver_outputs_and_statuses(use_graphs):
         if pipe is not None:
             pipe.close()
         az.az_net_free(net)
+
+
+@pytest.mark.parametrize("planes_out,max_legal", [(95, 6080), (95, 100), (1, 64), (73, 1)])
+def test_compact_policy_row_edges(planes_out, max_legal):
+    # rows with no, one, every and only the last cells legal, and a dense random
+    # one, at the longest and the shortest policy row: the compact row is the dense
+    # row's legal cells in order, truncated at max_legal, and the count is the true one
+    import paper_2609_37447_amd as az
+    import torch
+    shape = azgen.NetShape(in_planes=12, blocks=1, filters=8, policy_planes=planes_out, value_hidden=8)
+    blob = azgen.make_weights(shape, 951, alpha_fold=True, bf16=False)
+    rng = np.random.Generator(np.random.PCG64(952))
+    NM, B = shape.n_moves, 6
+    planes = (rng.random((B, 12, 8, 8)) < 0.3).astype(np.float32)
+    legal = np.zeros((B, NM), dtype=np.uint8)
+    legal[1, NM - 1] = 1
+    legal[2] = 255
+    legal[3, -20:] = 1
+    legal[4] = rng.random(NM) < 0.5
+    legal[5, 0] = 2
+    print(f"case compact edges P={planes_out} max_legal={max_legal}", flush=True)
+    spec = az.spec_from_shape(shape, B)
+    net = az.az_net_load(spec, blob, "f32")
+    try:
+        pol = torch.empty((B, NM), device="cuda")
+        val = torch.empty((B,), device="cuda")
+        az.eval_tensors(net, torch.from_numpy(planes).cuda(), torch.from_numpy(legal).cuda(), pol, val)
+        torch.cuda.synchronize()
+        dense = pol.cpu().numpy()
+        pipe = az.Pipeline(net, spec, B, 1, max_legal=max_legal)
+        try:
+            pl, lg, po, va, co = pipe.views[0]
+            pl[:], lg[:], po[:] = planes, legal, np.nan
+            pipe.submit(0, B)
+            if int((legal != 0).sum(axis=1).max()) > max_legal:
+                with pytest.raises(az.AzError):
+                    pipe.wait(0)
+            else:
+                pipe.wait(0)
+            for i in range(B):
+                want = dense[i][legal[i] != 0]
+                assert co[i] == len(want)
+                n = min(len(want), max_legal)
+                assert np.array_equal(po[i, :n], want[:n]) and np.all(po[i, n:] == 0.0)
+            assert np.array_equal(va, val.cpu().numpy())
+        finally:
+            pipe.close()
+    finally:
+        az.az_net_free(net)
