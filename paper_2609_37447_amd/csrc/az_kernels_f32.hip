@@ -38,6 +38,7 @@
 #include "az_internal.h"
 #include "az_mfma_common.h"
 
+#include <float.h>
 #include <math.h>
 
 namespace {
@@ -50,11 +51,21 @@ constexpr int CELLS = AZ_MAX_POLICY * 64;
 
 struct Split { bf16x8 h, m, l; };
 
-// x = h + m + l.  A part of a non-finite x is x itself, the others zero.
+// x = h + m + l; a finite x that rounds past the largest bf16 takes that as its h.
+// Of a non-finite x, h is x and the others are zero.
 __device__ __forceinline__ void split3(float x, uint32_t& h, uint32_t& m, uint32_t& l) {
   h = bf16_bits(x);
-  const float hf = __uint_as_float(h << 16);
-  const float r = fabsf(hf) < INFINITY ? x - hf : 0.0f;
+  const bool finite = fabsf(x) < INFINITY;
+  if (finite && (h & 0x7fffu) == 0x7f80u) --h;
+  const float r = finite ? x - __uint_as_float(h << 16) : 0.0f;
+  m = bf16_bits(r);
+  l = bf16_bits(r - __uint_as_float(m << 16));
+}
+// The same for 0 <= x < BIG.
+constexpr float BIG = 0x1.fep127f;  // the largest bf16
+__device__ __forceinline__ void split3_small(float x, uint32_t& h, uint32_t& m, uint32_t& l) {
+  h = bf16_bits(x);
+  const float r = x - __uint_as_float(h << 16);
   m = bf16_bits(r);
   l = bf16_bits(r - __uint_as_float(m << 16));
 }
@@ -72,6 +83,12 @@ __device__ __forceinline__ void mma_split(const Split& a, const Split& x, f32x4&
   small = mma16(a.m, x.h, small);
   small = mma16(a.h, x.m, small);
 }
+
+// The sum of the two accumulators.  Where an operand or the sum is infinite the
+// leading products alone give what a chain of multiply-adds gives; the small ones (a
+// zero or negative part times the infinity) are infinite or NaN, and the median is
+// then a finite value.
+__device__ __forceinline__ float mma_sum(float c, float small) { return c + med3(small, -FLT_MAX, FLT_MAX); }
 
 __device__ __forceinline__ bf16x8 frag_at(const uint8_t* p) { return *reinterpret_cast<const bf16x8*>(p); }
 
@@ -195,28 +212,42 @@ __global__ __launch_bounds__(NT) void az_net_f32_kernel(AzDevNet p, const float*
     }
     __syncthreads();  // every wave has read the buffer
     if (busy) {
+      float most = 0.0f;
 #pragma unroll
       for (int m = 0; m < MB; ++m) {
         const float bv[4] = {bb[m].x, bb[m].y, bb[m].z, bb[m].w};
 #pragma unroll
-        for (int n = 0; n < NB; ++n) {
-          uint32_t h[4], md[4], l[4];
+        for (int n = 0; n < NB; ++n)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            float y = acc[m][n][r] + sml[m][n][r] + bv[r];
+            float y = mma_sum(acc[m][n][r], sml[m][n][r]) + bv[r];
             if (residual) y += res[m][n][r];
             y = act_fn(y, cap);
             if (residual || last) res[m][n][r] = y;
-            split3(y, h[r], md[r], l[r]);
+            acc[m][n][r] = y;
+            most = fmaxf(most, y);
           }
-          if (mb0 + m < M16) {
-            uint8_t* dst = sm + ((nb0 + n + 4 * hi4 + 1) * 9 + col + 1) * CS + (mb0 + m) * 32 + kq * 8;
-            *reinterpret_cast<uint2*>(dst) = make_uint2(h[0] | h[1] << 16, h[2] | h[3] << 16);
-            *reinterpret_cast<uint2*>(dst + RB) = make_uint2(md[0] | md[1] << 16, md[2] | md[3] << 16);
-            *reinterpret_cast<uint2*>(dst + 2 * RB) = make_uint2(l[0] | l[1] << 16, l[2] | l[3] << 16);
-          }
-        }
       }
+      auto store = [&](auto split) {
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+#pragma unroll
+          for (int n = 0; n < NB; ++n) {
+            uint32_t h[4], md[4], l[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) split(acc[m][n][r], h[r], md[r], l[r]);
+            if (mb0 + m < M16) {
+              uint8_t* dst = sm + ((nb0 + n + 4 * hi4 + 1) * 9 + col + 1) * CS + (mb0 + m) * 32 + kq * 8;
+              *reinterpret_cast<uint2*>(dst) = make_uint2(h[0] | h[1] << 16, h[2] | h[3] << 16);
+              *reinterpret_cast<uint2*>(dst + RB) = make_uint2(md[0] | md[1] << 16, md[2] | md[3] << 16);
+              *reinterpret_cast<uint2*>(dst + 2 * RB) = make_uint2(l[0] | l[1] << 16, l[2] | l[3] << 16);
+            }
+          }
+      };
+      // checked once for the wave's values: a check in every split costs 2 to 4% of
+      // the network
+      if (__builtin_expect(__any(most >= BIG), 0)) store([](float x, uint32_t& h, uint32_t& m, uint32_t& l) { split3(x, h, m, l); });
+      else store([](float x, uint32_t& h, uint32_t& m, uint32_t& l) { split3_small(x, h, m, l); });
     }
     __syncthreads();
   };
@@ -289,7 +320,7 @@ __global__ __launch_bounds__(NT) void az_net_f32_kernel(AzDevNet p, const float*
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int row = (rb0 + 2 * i) * 16 + 4 * kq + r;
-        if (row <= P) L[row * 64 + (nb + 4 * hi4) * 8 + col] = acc[i][r] + sml[i][r] + p.head_b[row];
+        if (row <= P) L[row * 64 + (nb + 4 * hi4) * 8 + col] = mma_sum(acc[i][r], sml[i][r]) + p.head_b[row];
       }
   }
   __syncthreads();
@@ -330,7 +361,7 @@ __global__ __launch_bounds__(NT) void az_net_f32_kernel(AzDevNet p, const float*
       sum += e[i][t];
     }
   sum = block_reduce(sum, false, scratch + NW);
-  const float part = block_reduce(f2 * fmaxf(g, 0.0f), false, scratch + 2 * NW);
+  const float part = block_reduce(f2 * (unit ? fmaxf(g, 0.0f) : 0.0f), false, scratch + 2 * NW);
   const float inv = sum > 0.0f ? 1.0f / sum : 0.0f;
   float* pol = policy + (size_t)b * NM;
 #pragma unroll

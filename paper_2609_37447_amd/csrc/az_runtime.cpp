@@ -280,16 +280,17 @@ void pack_conv(const float* W, const float* wscale, int F, int Cin, int Cp, Kind
   }
 }
 
-// The bf16 parts h, m, l of an fp32 weight w = h + m + l; a part of a non-finite
-// value is the value itself, the others zero.
+// The bf16 parts h, m, l of an fp32 weight w = h + m + l, h at most the largest
+// bf16 for a finite w; of a non-finite one h is w and the others are zero.
 void split3(float x, uint32_t* parts) {
   for (int i = 0; i < 3; ++i) {
-    const uint16_t h = bf16_rne(x);
-    const uint32_t u = (uint32_t)h << 16;
+    uint32_t h = bf16_rne(x);
+    if (isfinite(x) && (h & 0x7fffu) == 0x7f80u) --h;
+    const uint32_t u = h << 16;
     float f;
     memcpy(&f, &u, 4);
     parts[i] = h;
-    x = isfinite(f) ? x - f : 0.0f;
+    x = isfinite(x) ? x - f : 0.0f;
   }
 }
 
@@ -309,7 +310,7 @@ void pack_split(const float* W, int rows, int chans, std::vector<uint8_t>& out) 
       const int n = (chans - c0 < 8 ? chans - c0 : 8) * TAPS;
       uint32_t u[N] = {}, part[3][N];
       memcpy(u, W + ((size_t)row * chans + c0) * TAPS, n * sizeof(float));
-      uint32_t big = 0;  // a value that is not finite, or not once rounded
+      uint32_t big = 0;  // a value that is not finite, or rounds past the largest bf16
       for (int i = 0; i < N; ++i) big |= (u[i] & 0x7fffffffu) >= 0x7f7f8000u;
       if (big) {
         for (int i = 0; i < N; ++i) {

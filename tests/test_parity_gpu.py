@@ -496,6 +496,103 @@ def test_f32_filter_counts(filters):
         H.compare_f32(Pg, Vg, Pr, Vr)
 
 
+def _arrays(shape, blob):
+    """{name: view of the blob}."""
+    out, off = {}, 0
+    for name, shp in shape.layer_sizes():
+        n = int(np.prod(shp))
+        out[name] = blob[off:off + n].reshape(shp)
+        off += n
+    return out
+
+
+# filter counts of the four wave tiles
+@pytest.mark.parametrize("filters", [8, 40, 72, 136])
+@pytest.mark.parametrize("where", ["plane", "weight", "sum"])
+def test_f32_infinities_follow_the_multiply_add_chain(filters, where):
+    # An infinite plane, an infinite weight and sums that overflow give the sign's
+    # infinity, as a chain of multiply-adds does, and the activation then the cap or
+    # zero.  No sum meets both infinities or 0 * inf, so the float64 network, whose
+    # sums do not overflow, has the same finite outputs.
+    shape = azgen.NetShape(in_planes=13, blocks=2, filters=filters, policy_planes=3, value_hidden=32, act_cap=6.0)
+    blob = azgen.make_weights(shape, 960 + filters, alpha_fold=True, bf16=False)
+    _scale_fc2(shape, blob, 1.0 / 8)
+    A = _arrays(shape, blob)
+    planes, legal = _shape_inputs(shape, 5, 17)
+    sign = np.where(np.arange(filters) % 3 == 1, -1.0, 1.0).astype(np.float32)
+    if where == "plane":
+        planes[np.arange(5), np.arange(5), np.arange(5), 3] = np.inf
+    elif where == "weight":
+        planes[:, 12] = 1.0
+        A["stem.w"][:, 12] = 0.0
+        A["stem.w"][:filters // 2, 12, 1, 1] = sign[:filters // 2] * np.float32(np.inf)
+    else:
+        A["stem.w"][:] = 1024 * (4.0 + np.abs(A["stem.w"])) * sign[:, None, None, None]
+        planes[:, :12] *= np.float32(3e38)
+    _print(f"case f32 infinities F={filters} {where}")
+    Pr, Vr = O.forward(shape, blob, planes, legal)
+    assert np.all(np.isfinite(Pr)) and np.all(np.isfinite(Vr))
+    Pg, Vg = H.gpu_eval(shape, blob, "f32", planes, legal)
+    H.assert_policy_structure(Pg, legal)
+    H.compare_f32(Pg, Vg, Pr, Vr)
+
+
+@pytest.mark.parametrize("filters", [8, 40, 72, 136])
+def test_f32_infinite_activations(filters):
+    # Without a cap an infinite plane makes infinite activations, which every layer
+    # carries on: weights of one sign from there on, so that no sum meets both
+    # infinities, policy logits of -inf (prior 0) around the corner and a value of 1.
+    shape = azgen.NetShape(in_planes=12, blocks=1, filters=filters, policy_planes=3, value_hidden=32)
+    blob = azgen.make_weights(shape, 980 + filters, alpha_fold=True, bf16=False)
+    A = _arrays(shape, blob)
+    A["stem.w"][:, 3] = np.abs(A["stem.w"][:, 3])
+    for name, f in (("block0.w1", 0.05), ("block0.w2", 0.05), ("policy.w", -0.02), ("value.w", 0.02),
+                    ("fc1.w", 0.05), ("fc2.w", 0.02)):
+        A[name][:] = np.float32(f) * np.abs(A[name])
+    planes, legal = _shape_inputs(shape, 5, 19)
+    legal[2:] = 1
+    planes[2:, 3, 0, 0] = np.inf
+    _print(f"case f32 infinite activations F={filters}")
+    Pr, Vr = O.forward(shape, blob, planes, legal)
+    assert np.all(np.isfinite(Pr)) and np.all(Vr[2:] == 1.0) and np.all(Vr[:2] < 0.99)
+    assert np.all((Pr[2:].reshape(3, 3, 8, 8) == 0.0).sum(axis=(2, 3)) == 16)
+    Pg, Vg = H.gpu_eval(shape, blob, "f32", planes, legal)
+    H.assert_policy_structure(Pg, legal)
+    H.compare_f32(Pg, Vg, Pr, Vr)
+
+
+@pytest.mark.parametrize("filters", [8, 40, 72, 136])
+@pytest.mark.parametrize("where", ["planes", "weights"])
+def test_f32_largest_finite_values(filters, where):
+    # Planes or stem weights within 2^-8 of the largest float (past the largest
+    # bf16) are finite values: the network scaled by powers of two, 2^127 on one
+    # stem operand, 2^-100 on the other and 2^-27 in the heads, is the plain one.
+    shape = azgen.NetShape(in_planes=12, blocks=1, filters=filters, policy_planes=3, value_hidden=32)
+    blob = azgen.make_weights(shape, 970 + filters, alpha_fold=True, bf16=False)
+    _scale_fc2(shape, blob, 1.0 / 8)
+    planes, legal = _shape_inputs(shape, 5, 18)
+    rng = np.random.Generator(np.random.PCG64(971))
+    big = lambda n: np.float32(2.0) - np.float32(2.0 ** -7) * rng.random(n, dtype=np.float32)  # noqa: E731
+    A = _arrays(shape, blob)
+    if where == "planes":
+        planes *= big(planes.shape)
+    else:
+        A["stem.w"][:, :, 1, 1] = big((filters, 12)) * np.where(rng.random((filters, 12)) < 0.5, -1, 1)
+    Pr, Vr = O.forward(shape, blob, planes, legal)
+    up, down = np.float32(2.0 ** 127), np.float32(2.0 ** -100)
+    planes *= up if where == "planes" else down
+    A["stem.w"][:] *= down if where == "planes" else up
+    assert max(np.abs(planes).max(), np.abs(A["stem.w"]).max()) > 3.39e38
+    for name in ("stem.b", "block0.b1", "block0.b2"):
+        A[name][:] *= np.float32(2.0 ** 27)
+    for name in ("policy.w", "value.w"):
+        A[name][:] *= np.float32(2.0 ** -27)
+    _print(f"case f32 largest finite {where} F={filters}")
+    Pg, Vg = H.gpu_eval(shape, blob, "f32", planes, legal)
+    H.assert_policy_structure(Pg, legal)
+    H.compare_f32(Pg, Vg, Pr, Vr)
+
+
 # --------------------------------------------------------------------------- #
 # Deployment validation (per-row comparison kernel and the validate() gate)
 # --------------------------------------------------------------------------- #
