@@ -5,10 +5,14 @@
 // h = bf16(x), m = bf16(x - h), l = x - h - m (8 + 8 + 8 significant bits), and a
 // product w * x is taken as the six part products of weight 2^-16 or more: hw hx
 // into one fp32 accumulator, lw hx, hw lx, mw mx, mw hx and hw mx into another.
-// Each is exact in fp32; what is left out is below 2^-25 of the product, under the
-// rounding of one fp32 multiply-add, and the leading accumulator is rounded once
-// per 32 channels where the multiply-add chain was once per channel.  Distance from
-// float64 (2-norm, policy / value; in brackets fp32 multiply-adds on the vector
+// Each is exact in fp32.  What is left out, m l + l m + l l of parts of at most
+// 2^-8 (m) and 2^-17 (l) of their operand's power of two, is at most 2^-24 of the
+// product (random operands in [1, 2) reach 2^-24.3): about the rounding of one fp32
+// multiply-add.  The sums gain: the leading accumulator is rounded once per 32
+// channels where the multiply-add chain was once per channel.  Operands below 2^-110
+// lose low bits of l to bf16's range, and a sum whose leading products overflow is
+// infinite within 2^-8 of the largest float.  Distance from float64 (2-norm, policy /
+// value; in brackets fp32 multiply-adds on the vector
 // ALUs, which this replaces): 2x32 1.3e-7 / 2.1e-7 (3.6e-7 / 4.1e-7), 20x128 3.2e-7 /
 // 9.2e-7 (7.3e-7 / 2.3e-6), 2x256 2.0e-7 / 5.6e-7 (5.9e-7 / 1.2e-6).  With all six
 // in one accumulator it was no better than the chain.  The bf16 instruction runs at
@@ -22,7 +26,9 @@
 // channel blocks x NB square blocks, chosen so that one pass covers the layer:
 // 1 x 1 up to 16 filters, 1 x 2 up to 64, 1 x 4 up to 128, 2 x 4 up to 256 (32
 // filters: 1 x 1 20.7 us, 1 x 2 19.6 us; 64: 1 x 2 33 us, 1 x 4 36 us: the waves that
-// share a channel block each stream its weights through the L1).
+// share a channel block each stream its weights through the L1).  The 2 x 4 tile does
+// not fit the 256 registers two waves a SIMD leave each: 53 of them spill, 216 bytes
+// of scratch a lane, on every network above 128 filters.
 //
 // LDS holds one activation buffer: [square slot][part h, m, l][channel].  Slots
 // are 9 to a row with zero rows above and below the board and one zero column
@@ -34,7 +40,7 @@
 // What bounds it: the six products (27.6k MFMA cycles a 128-filter convolution on
 // the one compute unit a board has, 0.46 ms for 20x128) and, on small networks, the
 // latency of the layers' chain.  20x128, 64 boards: 13.5 ms -> 0.68 ms; 2x32, 16
-// boards: 100 -> 20 us; 1,024 boards: 343 -> 79 us; 2x256, 16 boards: 5.7 -> 0.27 ms.
+// boards: 100 -> 19.6 us; 1,024 boards: 343 -> 79 us; 2x256, 16 boards: 5.7 -> 0.27 ms.
 #include "az_internal.h"
 #include "az_mfma_common.h"
 
@@ -378,7 +384,8 @@ hipError_t launch(const AzDevNet& n, const float* planes, const uint8_t* legal, 
   const int slot = 3 * 64 * ((n.filters + 31) / 32) + 16;
   const int act = SLOTS * slot, logits = (n.policy_planes + 1) * 64 * 4;
   const int scratch_off = act > logits ? act : logits;  // multiples of 16
-  const int lds = scratch_off + 3 * NW * 4;  // 144.3 KB at 256 filters
+  const int lds = scratch_off + 3 * NW * 4;
+  static_assert(SLOTS * (3 * 64 * (256 / 32) + 16) + 3 * NW * 4 == 141328, "LDS at 256 filters, of 160 KB");
   if (lds > 64 * 1024) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&az_net_f32_kernel<MB, NB>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, lds);
