@@ -81,7 +81,7 @@ COUNTERS = {
     ("net24x256_bf16_b1024", 1, 1024): ("f3d1ea1427b3ea1e798d96c1f19dadedeb5c17cff4c87c38eae7b0ff52a63e09", 450562.8, 18704.1, 0.8273),
     ("deployed14x160_int8_b1024", 1, 1024): ("fc736842338dfe2064cd505dac3abeef8a7968170061d8a6636ae6df55049899", 35423.5, 7552.0, 0.4916),
     ("deployed14x160_int8_b1024", 2, 64): ("fc736842338dfe2064cd505dac3abeef8a7968170061d8a6636ae6df55049899", 29223.9, 472.0, 0.0732),
-    ("deployed14x160_bf16_b1024", 2, 1024): ("fc736842338dfe2064cd505dac3abeef8a7968170061d8a6636ae6df55049899", 114946.9, 7536.0, 0.5637),
+    ("deployed14x160_bf16_b1024", 1, 1024): ("fc736842338dfe2064cd505dac3abeef8a7968170061d8a6636ae6df55049899", 114946.9, 7536.0, 0.5637),
     ("tiny_2x32_f32_b16", 0, 16): ("1aa299be26c797c412efab26d28cfe7012f75cfb22005dbb3afff0d58b7a026b", 1416.0, 292.5, 0.0078),
 }
 

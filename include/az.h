@@ -228,20 +228,19 @@ int az_net_moves(const az_net* net);
 
 /* Kernel tiling used by az_eval_batch.  0: chosen from B and the dtype
  * (default); 1 (large): four boards per workgroup (F = 64, 128) or two
- * (F = 256), one workgroup per compute unit; 2 (small): the fewest boards per
- * workgroup that place the batch on the compute units in one round: one up to a
- * board per compute unit, then two, then as the large tiling; 3 (medium, F = 64
- * and 128 only): two boards per workgroup, two workgroups per compute unit (one
- * for AZ_BF16 with F = 128).  The deployed network has two: 1, one wave per
- * board, four per compute unit (AZ_INT8), or two boards per workgroup of four waves
- * (AZ_BF16); 2, four waves for one board up to a board per compute unit, for two
- * boards up to two, then as tiling 1.  Every tiling computes bitwise the
- * same results.  AZ_F32 has a single tiling and accepts only 0.  Returns
- * AZ_OK or AZ_ERR_INVALID_ARG. */
+ * (F = 256), one workgroup per compute unit; 2 (small): one board per
+ * workgroup; 3 (medium, F = 64 and 128 only): two boards per workgroup, two
+ * workgroups per compute unit (one for AZ_BF16 with F = 128).  The deployed
+ * network has two to choose from: 1, one wave per board, four per compute unit
+ * (AZ_INT8), or two boards per workgroup of four waves (AZ_BF16); 2, four waves
+ * per board.  A tiling other than 0 runs for every B.  Every tiling computes
+ * bitwise the same results.  AZ_F32 has a single tiling and accepts only 0.
+ * Returns AZ_OK or AZ_ERR_INVALID_ARG. */
 int az_net_set_tiling(az_net* net, int32_t tiling);
 
-/* The tiling az_eval_batch would use for a batch of B (1, 2 or 3; 0 for
- * AZ_F32), or a negative status. */
+/* The tiling az_eval_batch runs for a batch of B (1, 2 or 3; 0 for AZ_F32), or
+ * a negative status.  3 for the deployed network (AZ_INT8): two boards per
+ * workgroup of four waves, which only the automatic choice takes. */
 int az_net_tiling_for(const az_net* net, int32_t B);
 
 /* Device bytes held by the handle (packed weights and per-layer constants). */

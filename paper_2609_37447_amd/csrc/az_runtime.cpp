@@ -420,54 +420,42 @@ std::vector<uint32_t> fromto_actions() {
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Deployed network.  The tiling (az_net_tiling_for): 2 while the batch has at most
-// two boards per compute unit, 1 beyond it, and for bf16 2 again past three.
-int choose_dep_tiling(const az_net* n, int B) {
-  const bool i8 = n->dtype == AZ_INT8;
-  const long per1 = (long)n->cus * (i8 ? 4 : 3), per2 = n->cus;
-  const long r1 = (B + per1 - 1) / per1, r2 = (B + per2 - 1) / per2;
-  return r2 * 10 < r1 * (i8 ? 25 : 28) ? 2 : 1;
-}
-
-// Boards per workgroup of the deployed network's kernel (0: a wave per board).
-// Measured on 14x160 with 256 compute units (us; one / two boards per workgroup /
-// a wave per board): int8 256 boards 143 / 200 / 337, 333 boards 297 / 200 / 337, 512
-// boards 298 / 228 / 338, 600 boards - / 418 / 338, 1,024 boards 592 / 424 / 365; bf16
-// 256 boards 214 / 290 / -, 333 boards 427 / 293 / -, 1,024 boards 888 / 670 / -.
-int dep_boards(const az_net* n, int tiling, int B) {
-  const bool i8 = n->dtype == AZ_INT8;
-  if (tiling == 1) return i8 ? 0 : 2;
-  if (B <= n->cus) return 1;
-  return !i8 || B <= 2 * n->cus ? 2 : 0;
-}
-
-int choose_tiling(const az_net* n, int B) {
-  if (n->dtype == AZ_F32) return 0;
-  if (n->tiling) return n->tiling;
-  if (is_deployed(n->spec)) return choose_dep_tiling(n, B);
-  const int F = n->spec.filters;
-  if (B < 512) return 2;
-  if (n->dtype == AZ_INT8) return B <= 768 ? 2 : 1;
-  if (n->dtype == AZ_BF16) return B >= 768 ? 1 : 2;
-  if (B <= 768) return 2;
-  if (B >= 1024) return 1;
-  return az_mfma_tiling_valid(F, 3) ? 3 : 1;
-}
-
-// The kernel a move-plane network's tiling runs for a batch of B.  The small tiling
-// takes the fewest boards per workgroup that place the batch on the compute units
-// in one round: a second workgroup on a compute unit costs more than a second
-// board in the first one, which shares its weight stream.  Measured on 20x128 with
-// 256 compute units (us per batch; one / two / four boards per workgroup):
+// The tiling a batch of B runs (the forced one, or the automatic choice), which is
+// what az_net_tiling_for reports: 0 for AZ_F32; 1 large, 2 small, 3 medium for a
+// move-plane network; for the deployed one 2 one board per workgroup of four waves,
+// 1 a wave per board (int8) or two boards per workgroup (bf16), 3 two boards per
+// workgroup (int8).
+//
+// The automatic choice takes the fewest boards per workgroup that place the batch
+// on the compute units in one round: a second workgroup on a compute unit costs more
+// than a second board in the first one, which shares its weight stream.
+//
+// Measured on 20x128 with 256 compute units (us per batch; one / two / four boards
+// per workgroup):
 //   int8  256 boards 97 / 136 / 232, 288 boards 148 / 136 / 233, 512 boards
 //         181 / 161 / 234, 576 boards 246 / 249 / 234, 768 boards 270 / 262 / 235
 //   bf16  256 boards 162 / 210 / 380, 288 boards 251 / 211 / 380, 512 boards
 //         312 / 280 / 382, 576 boards 414 / 481 / 383
 //   20x256 int8 (one / two boards) 256 boards 310 / 428, 320 boards 563 / 428
-int choose_kernel(const az_net* n, int B) {
-  const int t = choose_tiling(n, B), F = n->spec.filters;
-  if (t != 2 || B <= n->cus) return t;
-  return az_mfma_tiling_valid(F, 3) && B <= 2 * n->cus ? 3 : 1;
+// Deployed network, 14x160 (us; one / two boards per workgroup / a wave per board):
+//   int8  256 boards 143 / 200 / 337, 333 boards 297 / 200 / 337, 512 boards
+//         298 / 228 / 338, 600 boards - / 418 / 338, 1,024 boards 592 / 424 / 365
+//   bf16  256 boards 214 / 290 / -, 333 boards 427 / 293 / -, 1,024 boards 888 / 670 / -
+int choose_tiling(const az_net* n, int B) {
+  if (n->dtype == AZ_F32) return 0;
+  if (n->tiling) return n->tiling;
+  if (B <= n->cus) return 2;
+  if (is_deployed(n->spec)) return n->dtype == AZ_INT8 && B <= 2 * n->cus ? 3 : 1;
+  const bool medium = az_mfma_tiling_valid(n->spec.filters, 3);
+  if (B <= 2 * n->cus) return medium ? 3 : 1;
+  if (n->dtype == AZ_FP8_E4M3 && B > 768 && B < 1024) return medium ? 3 : 1;
+  return 1;
+}
+
+// Boards per workgroup of the deployed network's tiling (0: a wave per board).
+int dep_boards(const az_net* n, int tiling) {
+  if (tiling == 2) return 1;
+  return n->dtype == AZ_INT8 && tiling == 1 ? 0 : 2;
 }
 
 }  // namespace
@@ -836,11 +824,11 @@ int az_eval_batch_wdl(az_net* net, const float* planes, const uint8_t* legal, in
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (dep)
     e = (net->dtype == AZ_INT8 ? az_launch_deployed_int8 : az_launch_deployed_bf16)(
-        net->dn, dep_boards(net, choose_tiling(net, B), B), planes, legal, B, policy, value, wdl, s);
+        net->dn, dep_boards(net, choose_tiling(net, B)), planes, legal, B, policy, value, wdl, s);
   else if (net->dtype == AZ_F32)
     e = az_launch_f32(net->dn, planes, legal, B, policy, value, s);
   else
-    e = az_launch_mfma(net->dtype, choose_kernel(net, B), net->dn, planes, legal, B, policy, value, s);
+    e = az_launch_mfma(net->dtype, choose_tiling(net, B), net->dn, planes, legal, B, policy, value, s);
   if (cur != net->device) (void)hipSetDevice(cur);
   if (e != hipSuccess) return hip_fail(e, "kernel launch");
   return AZ_OK;

@@ -46,6 +46,48 @@ def gpu_eval(spec_shape, blob, dtype, planes, legal, w_scales=None, act_scales=N
     return outs[0] if repeat == 1 else outs
 
 
+def launched_grids(call):
+    """Workgroups (first grid dimension) of each kernel of this library that call
+    launches, from the profiler's trace."""
+    import json
+    import os
+    import tempfile
+
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as prof:
+        call()
+        torch.cuda.synchronize()
+    with tempfile.TemporaryDirectory() as d:
+        path = os.path.join(d, "trace.json")
+        prof.export_chrome_trace(path)
+        with open(path) as f:
+            events = json.load(f)["traceEvents"]
+    return [e["args"]["grid"][0] for e in events if e.get("cat") == "kernel" and "az_" in e.get("name", "")]
+
+
+def check_grids(spec, n_moves, blob, dtype, scales, sizes, boards, tilings):
+    """The launched grid of every forced tiling and the automatic choice (0) is that of
+    the tiling az_net_tiling_for names; boards: its boards per workgroup."""
+    import torch
+
+    import paper_2609_37447_amd as az
+    net = az.az_net_load(spec, blob, dtype, *scales)
+    try:
+        for B in sizes:
+            pl = torch.zeros((B, spec.in_planes, 8, 8), device="cuda")
+            lg = torch.ones((B, n_moves), dtype=torch.uint8, device="cuda")
+            pol, val = torch.empty((B, n_moves), device="cuda"), torch.empty((B,), device="cuda")
+            for t in (0,) + tilings:
+                az.az_net_set_tiling(net, t)
+                told = az.az_net_tiling_for(net, B)
+                assert t in (0, told)
+                assert launched_grids(lambda: az.eval_tensors(net, pl, lg, pol, val)) == [-(-B // boards[told])], (B, t)
+    finally:
+        az.az_net_free(net)
+
+
 @functools.lru_cache(maxsize=8)
 def quant_scales(wname: str, fmt: str, alpha_fold: bool = True):
     """(weight scales, activation scales) by absmax calibration on the workload's

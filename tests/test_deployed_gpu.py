@@ -11,7 +11,7 @@ stem's fp32 sums: on the CPU that flips 1 of the 10.5 M stem codes of the
 seeded 1,024-position batch, which moves that position by max|dP| 0.0044 and
 |dV| 0.0098, under a third of the tolerance.
 Tolerances: int8 max |dP| 3e-2 and |dV| 5e-2, bf16 1e-2 and 2e-2 (the WDL
-probabilities are held to the value tolerance).  Both kernel tilings (one wave
+probabilities are held to the value tolerance).  The kernel tilings (one wave
 per board, four waves per board) are run and must agree bitwise."""
 
 import numpy as np
@@ -20,6 +20,7 @@ import pytest
 import azgen
 from oracle import deployed as OD
 
+from . import _harness as H
 from ._harness import TOL, assert_policy_structure
 
 pytestmark = pytest.mark.gpu
@@ -226,10 +227,10 @@ def test_deployed_tilings_agree_bitwise(dtype):
 
 @pytest.mark.parametrize("dtype", ["int8", "bf16"])
 def test_deployed_board_counts(dtype):
-    # tiling 2 takes one board per workgroup up to a board per compute unit, then
-    # two, then (int8) a wave per board: around each step, with pooling blocks and an
-    # odd last workgroup, every row equals the one tiling 1 gives, and rows at the
-    # steps the oracle's
+    # the automatic choice takes one board per workgroup up to a board per compute
+    # unit, then two, then (int8) a wave per board: around each step, with pooling
+    # blocks and an odd last workgroup, every row equals the ones the forced tilings
+    # give, and rows at the steps the oracle's
     import torch
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     shape = _shape(2)
@@ -237,13 +238,14 @@ def test_deployed_board_counts(dtype):
     ws, acs = _scales(shape, blob) if dtype == "int8" else (None, None)
     planes, legal = _inputs(shape, 2 * cus + 3, 2266)
     for B in (cus, cus + 1, 2 * cus - 1, 2 * cus + 3):
-        two = gpu_eval(shape, blob, dtype, planes[:B], legal[:B], ws, acs, tiling=2)
-        one = gpu_eval(shape, blob, dtype, planes[:B], legal[:B], ws, acs, tiling=1)
-        for a, b in zip(two, one):
-            assert np.array_equal(a, b)
+        auto = gpu_eval(shape, blob, dtype, planes[:B], legal[:B], ws, acs)
+        for t in (1, 2):
+            forced = gpu_eval(shape, blob, dtype, planes[:B], legal[:B], ws, acs, tiling=t)
+            for a, b in zip(auto, forced):
+                assert np.array_equal(a, b), t
         rows = np.array([0, 1, 2, 3, B // 2, B - 2, B - 1])
         ref = _oracle_rows(shape, blob, dtype, planes[rows], legal[rows], ws, acs)
-        _check(tuple(x[rows] for x in two), ref, legal[rows], dtype)
+        _check(tuple(x[rows] for x in auto), ref, legal[rows], dtype)
 
 
 def test_deployed_rows_do_not_depend_on_the_batch():
@@ -257,28 +259,33 @@ def test_deployed_rows_do_not_depend_on_the_batch():
         assert np.array_equal(a[5:6], b)
 
 
-def test_deployed_tiling_choice():
-    # the tiling with fewer rounds x time per round on 256 compute units: four
-    # waves per board (256 boards a round) against one wave per board (1,024 int8
-    # or 768 bf16 boards a round, 2.5x / 2.8x as long)
+@pytest.mark.parametrize("dtype", ["int8", "bf16"])
+def test_deployed_tiling_choice(dtype):
+    # az_net_tiling_for names the kernel that runs: four waves per board up to a board
+    # per compute unit, two boards per workgroup (tiling 3 in int8, 1 in bf16) up to
+    # two, then tiling 1; forced tilings run for every batch, and the grids agree
     import paper_2609_37447_amd as az
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
     shape = _shape(2)
     blob = azgen.make_weights(shape, 1036, alpha_fold=True, bf16=True)
-    ws, acs = _scales(shape, blob)
-    want = {"int8": {1: 2, 64: 2, 256: 2, 512: 2, 513: 1, 768: 1, 1024: 1},
-            "bf16": {1: 2, 64: 2, 512: 2, 513: 1, 768: 1, 769: 2, 1024: 2}}
-    for dtype, cases in want.items():
-        net = az.az_net_load(az.spec_from_shape(shape, 1024), blob, dtype,
-                             *((ws, acs) if dtype == "int8" else (None, None)))
-        try:
-            assert {B: az.az_net_tiling_for(net, B) for B in cases} == cases
-            for t in (0, 1, 2):
-                assert az.az_net_set_tiling(net, t) == az.AZ_OK
-            assert az.az_net_tiling_for(net, 64) == 2
-            for t in (3, -1):
-                assert az.az_net_set_tiling(net, t, raise_on_error=False) == az.AZ_ERR_INVALID_ARG
-        finally:
-            az.az_net_free(net)
+    q = _scales(shape, blob) if dtype == "int8" else ()
+    two = 3 if dtype == "int8" else 1
+    want = {1: 2, cus // 4: 2, cus: 2, cus + 1: two, 2 * cus: two, 2 * cus + 1: 1, 3 * cus + 1: 1, 4 * cus: 1}
+    net = az.az_net_load(az.spec_from_shape(shape, 4 * cus), blob, dtype, *q)
+    try:
+        assert {B: az.az_net_tiling_for(net, B) for B in want} == want
+        for t in (1, 2):
+            assert az.az_net_set_tiling(net, t) == az.AZ_OK
+            assert {az.az_net_tiling_for(net, B) for B in want} == {t}
+        assert az.az_net_set_tiling(net, 0) == az.AZ_OK and az.az_net_tiling_for(net, 64) == 2
+        for t in (3, -1):
+            assert az.az_net_set_tiling(net, t, raise_on_error=False) == az.AZ_ERR_INVALID_ARG
+    finally:
+        az.az_net_free(net)
+    boards = {1: 1, 2: 1, 3: 2} if dtype == "int8" else {1: 2, 2: 1}
+    H.check_grids(az.spec_from_shape(shape, 4 * cus), shape.n_moves, blob, dtype, q,
+                  [cus - 1, cus + 1, 2 * cus + 1], boards, (1, 2))
 
 
 def test_deployed_validate_gate():

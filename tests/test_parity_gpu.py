@@ -268,30 +268,33 @@ def test_tilings_agree_bitwise(wname, dtype):
         assert np.array_equal(P, outs[0][0]) and np.array_equal(V, outs[0][1])
 
 
-@pytest.mark.parametrize("filters,dtype", [(64, "int8"), (128, "bf16"), (128, "int8"), (256, "bf16")])
-def test_small_tiling_board_counts(filters, dtype):
-    # The small tiling takes one board per workgroup up to a board per compute
+@pytest.mark.parametrize("filters,dtype", [(64, "int8"), (64, "bf16"), (128, "bf16"), (128, "int8"), (128, "fp8"),
+                                           (256, "bf16")])
+def test_automatic_tiling_board_counts(filters, dtype):
+    # The automatic choice takes one board per workgroup up to a board per compute
     # unit, then two, then four: around each step of that rule every row equals
-    # the large tiling's bit for bit, and sampled rows equal the oracle's (the
-    # edges of the batch and of the workgroups at the steps).
+    # those of the one-board and the large tiling bit for bit, and sampled rows equal
+    # the oracle's (the edges of the batch and of the workgroups at the steps).
     import torch
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    shape = azgen.NetShape(in_planes=20, blocks=1, filters=filters, policy_planes=73, value_hidden=64)
+    shape = azgen.NetShape(in_planes=12 if dtype == "fp8" else 20, blocks=1, filters=filters,
+                           policy_planes=40 if dtype == "fp8" else 73, value_hidden=64)
     blob = azgen.make_weights(shape, 910 + filters, alpha_fold=True, bf16=True)
     _scale_fc2(shape, blob, 1.0 / 8)
     ws = acs = None
-    if dtype == "int8":
+    if dtype != "bf16":
         ws = O.weight_scales(shape, blob, dtype)
         acs = O.act_scales_from_absmax(O.calibrate_absmax(shape, blob, _shape_inputs(shape, 64, 99)[0]), dtype)
     planes, legal = _shape_inputs(shape, 2 * cus + 3, 31)
     for B in (cus, cus + 1, 2 * cus, 2 * cus + 3):
-        _print(f"case small tiling {filters} {dtype} B={B}")
-        P2, V2 = H.gpu_eval(shape, blob, dtype, planes[:B], legal[:B], ws, acs, tiling=2)
-        P1, V1 = H.gpu_eval(shape, blob, dtype, planes[:B], legal[:B], ws, acs, tiling=1)
-        assert np.array_equal(P2, P1) and np.array_equal(V2, V1)
+        _print(f"case automatic tiling {filters} {dtype} B={B}")
+        P0, V0 = H.gpu_eval(shape, blob, dtype, planes[:B], legal[:B], ws, acs)
+        for t in (1, 2):
+            P, V = H.gpu_eval(shape, blob, dtype, planes[:B], legal[:B], ws, acs, tiling=t)
+            assert np.array_equal(P, P0) and np.array_equal(V, V0), t
         rows = np.array([0, 1, 2, 3, 5, B // 2, B - 4, B - 3, B - 2, B - 1])
         Pr, Vr = H.oracle_eval(shape, blob, dtype, planes[rows], legal[rows], ws, acs)
-        H.compare(P2[rows], V2[rows], Pr, Vr, dtype)
+        H.compare(P0[rows], V0[rows], Pr, Vr, dtype)
 
 
 def test_refit_equal_then_unequal_scales():
@@ -663,22 +666,41 @@ def test_validate_gate_passes_faithful_and_flags_broken():
 
 
 def test_tiling_choice_per_dtype():
-    # int8: the one-board tiling up to 768 boards (its 18-step weight ring makes it
-    # the fastest there), the large tiling beyond; fp8: one board up to 768, medium
-    # below 1024, large from 1024; bf16: one board below 768, large from 768
+    # az_net_tiling_for names the kernel that runs: one board per workgroup up to a
+    # board per compute unit, two boards (medium) up to two, the large tiling beyond
+    # (256 filters have no medium one); a forced tiling runs for every batch
     import paper_2609_37447_amd as az
-    shape, blob, ws, acs = _relu6_net()
-    want = {"int8": {1: 2, 64: 2, 511: 2, 512: 2, 768: 2, 769: 1, 1024: 1},
-            "fp8": {64: 2, 511: 2, 768: 2, 769: 3, 1023: 3, 1024: 1},
-            "bf16": {64: 2, 512: 2, 767: 2, 768: 1, 1024: 1}}
-    for dtype, cases in want.items():
-        if dtype == "bf16":
-            net = az.az_net_load(az.spec_from_shape(shape, 1024), blob, "bf16")
-        else:
-            w8 = O.weight_scales(shape, blob, dtype)
-            a8 = np.full(shape.n_act_scales(), np.float32(6.0 / (127.0 if dtype == "int8" else 448.0)), np.float32)
-            net = az.az_net_load(az.spec_from_shape(shape, 1024), blob, dtype, w8, a8)
-        try:
-            assert {B: az.az_net_tiling_for(net, B) for B in cases} == cases, dtype
-        finally:
-            az.az_net_free(net)
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    for filters in (64, 128, 256):
+        shape = azgen.NetShape(20, 1, filters, 73, 64)
+        blob = azgen.make_weights(shape, 41, alpha_fold=True, bf16=True)
+        m = 1 if filters == 256 else 3
+        want = {1: 2, cus // 4: 2, cus: 2, cus + 1: m, 2 * cus: m, 2 * cus + 1: 1, 4 * cus: 1, 4 * cus + 1: 1}
+        for dtype in ("int8", "fp8", "bf16"):
+            q = () if dtype == "bf16" else (O.weight_scales(shape, blob, dtype), np.full(3, 0.05, np.float32))
+            net = az.az_net_load(az.spec_from_shape(shape, 8 * cus), blob, dtype, *q)
+            try:
+                assert {B: az.az_net_tiling_for(net, B) for B in want} == want, (dtype, filters)
+                for t in (1, 2) if filters == 256 else (1, 2, 3):
+                    az.az_net_set_tiling(net, t)
+                    assert {az.az_net_tiling_for(net, B) for B in want} == {t}
+                az.az_net_set_tiling(net, 0)
+                assert az.az_net_tiling_for(net, cus) == 2
+            finally:
+                az.az_net_free(net)
+
+
+@pytest.mark.parametrize("filters,dtype", [(64, "bf16"), (128, "int8"), (256, "int8")])
+def test_the_reported_tiling_is_launched(filters, dtype):
+    # the grid of the launched kernel, from the profiler: its boards per workgroup are
+    # those of the tiling that az_net_tiling_for names, forced or chosen
+    import paper_2609_37447_amd as az
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    boards = {1: 2, 2: 1} if filters == 256 else {1: 4, 2: 1, 3: 2}
+    shape = azgen.NetShape(20, 1, filters, 73, 64)
+    blob = azgen.make_weights(shape, 42, alpha_fold=True, bf16=True)
+    q = () if dtype == "bf16" else (O.weight_scales(shape, blob, dtype), np.full(3, 0.05, np.float32))
+    sizes = [cus - 1, cus + 1, 2 * cus, 2 * cus + 1]
+    H.check_grids(az.spec_from_shape(shape, 4 * cus), shape.n_moves, blob, dtype, q, sizes, boards, tuple(boards))
