@@ -428,15 +428,26 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 //
 // The automatic choice takes the fewest boards per workgroup that place the batch
 // on the compute units in one round: a second workgroup on a compute unit costs more
-// than a second board in the first one, which shares its weight stream.
+// than a second board in the first one, which shares its weight stream.  Two
+// exceptions, where a compute unit has more than two boards and fewer than four: with
+// 64 filters the small tilings' workgroups leave it room for three (one board each)
+// or four (two each); with fp8 the large tiling, with registers for a ring of three
+// groups and a tail of one, is behind two medium workgroups up to three boards.
 //
-// Measured on 20x128 with 256 compute units (us per batch; one / two / four boards
-// per workgroup):
-//   int8  256 boards 97 / 136 / 232, 288 boards 148 / 136 / 233, 512 boards
-//         181 / 161 / 234, 576 boards 246 / 249 / 234, 768 boards 270 / 262 / 235
-//   bf16  256 boards 162 / 210 / 380, 288 boards 251 / 211 / 380, 512 boards
-//         312 / 280 / 382, 576 boards 414 / 481 / 383
-//   20x256 int8 (one / two boards) 256 boards 310 / 428, 320 boards 563 / 428
+// Measured with 256 compute units (us per batch; one / two (medium) / four boards per
+// workgroup, with 256 filters one / two; of the forced tilings, one box per line):
+//            288 boards       512              640              768              896              1,023
+//   20x128   int8  143/137/227, 169/155/232, 235/239/231, 249/247/233, 308/254/236, 325/274/252
+//            bf16  244/216/371, 301/277/394, 408/469/380, 445/470/392, 548/490/423, 594/534/464
+//            fp8   169/175/287, 191/188/288, 272/272/292, 284/283/292, 349/294/291, 362/305/296
+//   10x64    int8  48/35/55, 48/37/56, 51/52/56, 52/52/57, 56/54/57, 59/56/58
+//            bf16  63/48/73, 64/52/74, 69/72/75, 75/75/75, 84/79/80, 91/86/85
+//            fp8   62/46/72, 62/47/72, 64/66/73, 65/67/74, 69/66/73, 71/68/74
+//   6x256    int8  183/139, 189/157, 274/289, 282/290, 366/292, 375/311
+//            bf16  321/237, 356/308, 494/533, 534/533, 666/559, 707/610
+//            fp8   222/158, 226/176, 332/327, 347/327, 442/328, 451/347
+// At 256 boards one board per workgroup is ahead everywhere (20x128 int8 97 / 142 / 230,
+// 10x64 36 / 35 / 55, 6x256 99 / 147).
 // Deployed network, 14x160 (us; one / two boards per workgroup / a wave per board):
 //   int8  256 boards 143 / 200 / 337, 333 boards 297 / 200 / 337, 512 boards
 //         298 / 228 / 338, 600 boards - / 418 / 338, 1,024 boards 592 / 424 / 365
@@ -446,10 +457,11 @@ int choose_tiling(const az_net* n, int B) {
   if (n->tiling) return n->tiling;
   if (B <= n->cus) return 2;
   if (is_deployed(n->spec)) return n->dtype == AZ_INT8 && B <= 2 * n->cus ? 3 : 1;
-  const bool medium = az_mfma_tiling_valid(n->spec.filters, 3);
-  if (B <= 2 * n->cus) return medium ? 3 : 1;
-  if (n->dtype == AZ_FP8_E4M3 && B > 768 && B < 1024) return medium ? 3 : 1;
-  return 1;
+  const int F = n->spec.filters, per_cu = (B + n->cus - 1) / n->cus;
+  if (F == 256 || per_cu > 4) return 1;
+  if (per_cu == 2) return 3;
+  if (F == 64) return per_cu == 3 ? 2 : 3;
+  return n->dtype == AZ_FP8_E4M3 && per_cu == 3 ? 3 : 1;
 }
 
 // Boards per workgroup of the deployed network's tiling (0: a wave per board).

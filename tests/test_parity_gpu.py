@@ -271,10 +271,10 @@ def test_tilings_agree_bitwise(wname, dtype):
 @pytest.mark.parametrize("filters,dtype", [(64, "int8"), (64, "bf16"), (128, "bf16"), (128, "int8"), (128, "fp8"),
                                            (256, "bf16")])
 def test_automatic_tiling_board_counts(filters, dtype):
-    # The automatic choice takes one board per workgroup up to a board per compute
-    # unit, then two, then four: around each step of that rule every row equals
-    # those of the one-board and the large tiling bit for bit, and sampled rows equal
-    # the oracle's (the edges of the batch and of the workgroups at the steps).
+    # The automatic choice changes at one, two, three and four boards per compute unit:
+    # around each step every row equals those of the one-board and the large tiling
+    # bit for bit, and sampled rows equal the oracle's (the edges of the batch and of
+    # the workgroups at the steps).
     import torch
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     shape = azgen.NetShape(in_planes=12 if dtype == "fp8" else 20, blocks=1, filters=filters,
@@ -285,8 +285,8 @@ def test_automatic_tiling_board_counts(filters, dtype):
     if dtype != "bf16":
         ws = O.weight_scales(shape, blob, dtype)
         acs = O.act_scales_from_absmax(O.calibrate_absmax(shape, blob, _shape_inputs(shape, 64, 99)[0]), dtype)
-    planes, legal = _shape_inputs(shape, 2 * cus + 3, 31)
-    for B in (cus, cus + 1, 2 * cus, 2 * cus + 3):
+    planes, legal = _shape_inputs(shape, 4 * cus + 3, 31)
+    for B in (cus, cus + 1, 2 * cus, 2 * cus + 3, 3 * cus, 3 * cus + 1, 4 * cus, 4 * cus + 3):
         _print(f"case automatic tiling {filters} {dtype} B={B}")
         P0, V0 = H.gpu_eval(shape, blob, dtype, planes[:B], legal[:B], ws, acs)
         for t in (1, 2):
@@ -667,19 +667,24 @@ def test_validate_gate_passes_faithful_and_flags_broken():
 
 def test_tiling_choice_per_dtype():
     # az_net_tiling_for names the kernel that runs: one board per workgroup up to a
-    # board per compute unit, two boards (medium) up to two, the large tiling beyond
-    # (256 filters have no medium one); a forced tiling runs for every batch
+    # board per compute unit, then the rule in boards per compute unit that was
+    # measured for the filters and dtype; a forced tiling runs for every batch
     import paper_2609_37447_amd as az
     import torch
     cus = torch.cuda.get_device_properties(0).multi_processor_count
+    # filters, dtype: tilings up to 2, 3 and 4 boards per compute unit
+    rule = {(64, "int8"): (3, 2, 3), (64, "fp8"): (3, 2, 3), (64, "bf16"): (3, 2, 3),
+            (128, "int8"): (3, 1, 1), (128, "fp8"): (3, 3, 1), (128, "bf16"): (3, 1, 1),
+            (256, "int8"): (1, 1, 1), (256, "fp8"): (1, 1, 1), (256, "bf16"): (1, 1, 1)}
     for filters in (64, 128, 256):
         shape = azgen.NetShape(20, 1, filters, 73, 64)
         blob = azgen.make_weights(shape, 41, alpha_fold=True, bf16=True)
-        m = 1 if filters == 256 else 3
-        want = {1: 2, cus // 4: 2, cus: 2, cus + 1: m, 2 * cus: m, 2 * cus + 1: 1, 4 * cus: 1, 4 * cus + 1: 1}
         for dtype in ("int8", "fp8", "bf16"):
             q = () if dtype == "bf16" else (O.weight_scales(shape, blob, dtype), np.full(3, 0.05, np.float32))
             net = az.az_net_load(az.spec_from_shape(shape, 8 * cus), blob, dtype, *q)
+            want = {1: 2, cus // 4: 2, cus: 2, 4 * cus + 1: 1}
+            for k, t in zip((2, 3, 4), rule[filters, dtype]):
+                want[(k - 1) * cus + 1] = want[k * cus] = t
             try:
                 assert {B: az.az_net_tiling_for(net, B) for B in want} == want, (dtype, filters)
                 for t in (1, 2) if filters == 256 else (1, 2, 3):
@@ -702,5 +707,5 @@ def test_the_reported_tiling_is_launched(filters, dtype):
     shape = azgen.NetShape(20, 1, filters, 73, 64)
     blob = azgen.make_weights(shape, 42, alpha_fold=True, bf16=True)
     q = () if dtype == "bf16" else (O.weight_scales(shape, blob, dtype), np.full(3, 0.05, np.float32))
-    sizes = [cus - 1, cus + 1, 2 * cus, 2 * cus + 1]
+    sizes = [cus - 1, cus + 1, 2 * cus, 2 * cus + 1, 3 * cus + 1]
     H.check_grids(az.spec_from_shape(shape, 4 * cus), shape.n_moves, blob, dtype, q, sizes, boards, tuple(boards))
