@@ -297,7 +297,8 @@ __device__ __forceinline__ void dep_wdl(const AzDevNet& p, const float* U, float
 // wave (lane = 0..63) once the final tower output h is in LDS (int8: codes in H;
 // bf16: hi parts in H, lo parts in X): embedding, tokens, query-key logits and
 // promotion offsets, legal-action softmax, WDL value head.  Every wave of the
-// workgroup meets the one barrier inside (live: the wave has a position).
+// workgroup meets the one barrier inside, and does nothing else if it has no
+// position (live: it has one).
 template <int MK, int BPG>
 __device__ __forceinline__ void dep_heads(const AzDevNet& p, uint8_t* smem_all, const uint8_t* __restrict__ legal,
                                           float* __restrict__ policy, float* __restrict__ value,
@@ -317,7 +318,7 @@ __device__ __forceinline__ void dep_heads(const AzDevNet& p, uint8_t* smem_all, 
   // ---- embedding: E[row][sq] = sum_f Wemb[row][f] h[f][sq], rows = tokens then value channels
   f32x16 tok[DTB][2];   // token rows (accumulators, then values)
   f32x16 uacc[2];       // value rows 128..159
-  {
+  if (live) {
     const uint8_t* ew = static_cast<const uint8_t*>(p.emb_w) + (size_t)lane * 16;
     // A fragments of K step s in ring slot s % 4, loaded three steps ahead
     constexpr int ES = DF / 16, ER = 4;
@@ -1896,9 +1897,7 @@ az_dep_kernel(AzDevNet p, const float* __restrict__ planes, const uint8_t* __res
   if constexpr (BPG == 1) {
     dep_heads4<MK>(p, smem, legal, policy, value, wdl, b0, wave, lane);
   } else {
-    const int bd = wave % BPG;  // waves past the boards only meet the barrier
-    dep_heads<MK, BPG>(p, smem, legal, policy, value, wdl, b0 + bd < B ? b0 + bd : B - 1, bd,
-                       wave < BPG && b0 + bd < B, lane);
+    dep_heads<MK, BPG>(p, smem, legal, policy, value, wdl, b0 + wave, wave, wave < BPG && b0 + wave < B, lane);
   }
 }
 
