@@ -176,13 +176,11 @@ __device__ __forceinline__ double2 pool_row(const AzDevNet& p, const float* pt, 
   return make_double2(mx, sum);
 }
 
-// Folds the projected context c[o] of a pooling layer into regular channel o's
-// bias in the layer's constant slot: int8 slots hold qbias = b / a[n+1] in
-// float64, so c enters in code units (c / a[n+1]); bf16 slots hold b in fp32.
-template <bool QUANT>
+// Folds the projected context c of a pooling layer into regular channel o's bias in
+// an int8 layer's constant slot: it holds qbias = b / a[n+1] in float64, so c enters
+// in code units (c / a[n+1]).
 __device__ __forceinline__ void add_context(const AzDevNet& p, float* kslot, int o, double c, int n_conv) {
-  if constexpr (QUANT) reinterpret_cast<double*>(kslot)[o] += c * p.pool_cinv[n_conv];
-  else kslot[o] += (float)c;
+  reinterpret_cast<double*>(kslot)[o] += c * p.pool_cinv[n_conv];
 }
 
 // bf16 hi and lo parts of eight fp32 values: x = hi + lo within 2^-16 |x|.
@@ -963,21 +961,18 @@ az_dep_kernel1(AzDevNet p, const float* __restrict__ planes, const uint8_t* __re
     for (int m = 0; m < DNMB; ++m)
       dst[m] = __builtin_bit_cast(frag_t, __builtin_amdgcn_raw_buffer_load_b128(twr, tvoff, soff + m * 64 * T::FB, 0));
   };
-  // per-layer epilogue constants of conv index k (0 = stem): [bias F] floats, or
-  // [qbias F | qmul F] doubles, as lane-held 16-byte chunks loaded at the start
-  // of a layer and parked in LDS before its barrier
+  // per-layer epilogue constants of conv index k (0 = stem), [qbias F | qmul F | qres,
+  // qhi] doubles, as lane-held 16-byte chunks loaded at the start of a layer and
+  // parked in LDS before its barrier
   constexpr int KV = C::KSLOT / 16;                  // 16-byte chunks per slot
   constexpr int KPL = (KV + 63) / 64;                // per lane
   auto load_consts = [&](int k, float4(&dst)[KPL]) {
 #pragma unroll
     for (int t = 0; t < KPL; ++t) {
       const int i = lane + 64 * t;
-      const void* src;
-      if constexpr (QUANT)
-        src = i < DF / 2 ? p.qbias + (size_t)k * DF + 2 * i
-              : i < DF   ? p.qmul + (size_t)k * DF + 2 * (i - DF / 2)
-                         : p.qext + 2 * (size_t)k;
-      else src = p.bias + (size_t)k * DF + 4 * i;
+      const double* src = i < DF / 2 ? p.qbias + (size_t)k * DF + 2 * i
+                          : i < DF   ? p.qmul + (size_t)k * DF + 2 * (i - DF / 2)
+                                     : p.qext + 2 * (size_t)k;
       dst[t] = i < KV ? *reinterpret_cast<const float4*>(src) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
   };
@@ -1213,8 +1208,8 @@ az_dep_kernel1(AzDevNet p, const float* __restrict__ planes, const uint8_t* __re
           }
         }
         // regular channel o's bias takes c[o] (int8: in code units, c[o] / a[n+1])
-        add_context<QUANT>(p, kslot, lane, c0, n_conv);
-        if (lane + 64 < DFR) add_context<QUANT>(p, kslot, lane + 64, c1, n_conv);
+        add_context(p, kslot, lane, c0, n_conv);
+        if (lane + 64 < DFR) add_context(p, kslot, lane + 64, c1, n_conv);
         zero_pads(GT{}, OFF_T);  // (1) wrote over them
         wave_lds_sync();
       }
@@ -1309,6 +1304,7 @@ az_dep_kernel(AzDevNet p, const float* __restrict__ planes, const uint8_t* __res
   constexpr int OFF_H = C::OFF_H, OFF_T = C::OFF_T, NBK = GT::NBK;
   constexpr int NWV = 4, NT = 64 * NWV;
   static_assert(DNMB == NWV + 1, "four waves, five channel blocks");
+  static_assert(BPG == 1 || BPG == 2, "boards per workgroup");
 
   __shared__ __attribute__((aligned(16))) uint8_t smem[C::SMEM];
 
@@ -1723,39 +1719,31 @@ az_dep_kernel(AzDevNet p, const float* __restrict__ planes, const uint8_t* __res
           }
           wave_lds_sync();
           // (3) c[o] = sum_i Wg[o][i] g[i] in fp64 (fp32 weights are exact): thread
-          //     t takes output t % 128 of boards t / 128, t / 128 + 2; the pooled
-          //     channels keep their bias (their codes are read by nothing)
+          //     t takes output t % 128 of board t / 128; the pooled channels keep
+          //     their bias (their codes are read by nothing)
           {
-            constexpr int NB2 = BPG > 2 ? 2 : 1;
-            const int bd0 = tid >> 7;
-            double co[NB2] = {};
-            if (bd0 < BPG) {
+            const int bd = tid >> 7;
+            if (bd < BPG) {
+              const double* gi = pg + bd * 2 * DG;
+              double co = 0.0;
 #pragma unroll
               for (int i4 = 0; i4 < NWP; ++i4) {
                 const float4 w = wpool[i4];
-#pragma unroll
-                for (int k = 0; k < NB2; ++k) {
-                  const double* gi = pg + (bd0 + 2 * k) * 2 * DG + 4 * i4;
-                  co[k] = __builtin_fma((double)w.x, gi[0], co[k]);
-                  co[k] = __builtin_fma((double)w.y, gi[1], co[k]);
-                  co[k] = __builtin_fma((double)w.z, gi[2], co[k]);
-                  co[k] = __builtin_fma((double)w.w, gi[3], co[k]);
-                }
+                co = __builtin_fma((double)w.x, gi[4 * i4 + 0], co);
+                co = __builtin_fma((double)w.y, gi[4 * i4 + 1], co);
+                co = __builtin_fma((double)w.z, gi[4 * i4 + 2], co);
+                co = __builtin_fma((double)w.w, gi[4 * i4 + 3], co);
               }
-#pragma unroll
-              for (int k = 0; k < NB2; ++k) {
-                const int bd = bd0 + 2 * k;
-                if constexpr (QUANT) {
-                  const double* kb = reinterpret_cast<const double*>(kslot);
-                  double* pb = reinterpret_cast<double*>(smem + C::OFF_PB) + bd * DF;
-                  pb[po] = po < DFR ? kb[po] + co[k] * p.pool_cinv[n_conv] : kb[po];
-                  if (po < DF - 128) pb[128 + po] = kb[128 + po];
-                } else {
-                  const float* kb = reinterpret_cast<const float*>(kslot);
-                  float* pb = reinterpret_cast<float*>(smem + C::OFF_PB) + bd * DF;
-                  pb[po] = po < DFR ? kb[po] + (float)co[k] : kb[po];
-                  if (po < DF - 128) pb[128 + po] = kb[128 + po];
-                }
+              if constexpr (QUANT) {
+                const double* kb = reinterpret_cast<const double*>(kslot);
+                double* pb = reinterpret_cast<double*>(smem + C::OFF_PB) + bd * DF;
+                pb[po] = po < DFR ? kb[po] + co * p.pool_cinv[n_conv] : kb[po];
+                if (po < DF - 128) pb[128 + po] = kb[128 + po];
+              } else {
+                const float* kb = reinterpret_cast<const float*>(kslot);
+                float* pb = reinterpret_cast<float*>(smem + C::OFF_PB) + bd * DF;
+                pb[po] = po < DFR ? kb[po] + (float)co : kb[po];
+                if (po < DF - 128) pb[128 + po] = kb[128 + po];
               }
             }
           }

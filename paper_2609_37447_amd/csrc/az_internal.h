@@ -17,8 +17,10 @@
 // Device-side description of a loaded network, passed to kernels by value.
 struct AzDevNet {
   int in_planes, blocks, filters, policy_planes, value_hidden, value_conv_relu;
-  float act_cap;     // +inf when the activation is a plain ReLU
-  float head_scale;  // value of one code of the final tower tensor (1 for float nets)
+  int pool_every;      // deployed network: 0 = no pooling blocks
+  int value_channels;  // deployed network: V
+  float act_cap;       // +inf when the activation is a plain ReLU
+  float fc2_b;
   // MFMA dtypes: A-fragment streams (see az_runtime.cpp for the order).
   // AZ_F32: A fragments of the weights' three bf16 parts.
   const void* stem_w;
@@ -35,30 +37,24 @@ struct AzDevNet {
   const double* qmul;
   const double* qbias;
   // Quantised nets, per output tensor k = 0..2*blocks (tensor k is written by
-  // conv k-1, the stem for k = 0): qres[k] = a[k-2] / a[k] for the second conv
-  // of a block (its residual input's code scaled into the output's code units),
-  // qhi[k] = the largest code of tensor k, min(qmax, act_cap / a[k]) rounded to
-  // the code grid (activation cap and saturation).
-  const double* qres;
+  // conv k-1, the stem for k = 0): qhi[k] = the largest code of tensor k, min(qmax,
+  // act_cap / a[k]) rounded to the code grid (activation cap and saturation).
+  // qext[2k], qext[2k + 1] = qres[k], qhi[k] side by side, for kernels that stage
+  // them with the per-channel constants; qres[k] = a[k-2] / a[k] for the second conv
+  // of a block (its residual input's code scaled into the output's code units).
   const float* qhi;
-  // qext[2k], qext[2k + 1] = qres[k], qhi[k] (as a double): the two scalars of
-  // tensor k side by side, for kernels that stage them with the per-channel ones
   const double* qext;
   const float* head_b;  // [AZ_HEAD_ROWS]: policy biases, value conv bias at row P, zeros
-  const float* fc1_w;   // [H][64]
   const float* fc1_b;   // [H]
   const float* fc2_w;   // [H]
-  float fc2_b;
-  // MFMA kernels: per head row scale and bias (policy rows times log2(e), value
-  // row P as is, zero padding) and fc1 as [64/4][H][4] (see az_runtime.cpp)
+  // fc1 as [64/4][H][4]; MFMA kernels: per head row scale and bias (policy rows times
+  // log2(e), value row P as is, zero padding; see az_runtime.cpp)
   const float* head_sc;  // [AZ_HEAD_ROWS]
   const float* head_bc;  // [AZ_HEAD_ROWS]
   const float* fc1_t;    // [16][H][4]
 
   // Deployed network (global pooling, from-to policy head, WDL value head); see
   // az_dep_kernel.h for the fragment orders.
-  int pool_every;      // 0: no pooling blocks
-  int value_channels;  // V
   const void* emb_w;   // bf16 A fragments, rows: D token rows, V value rows, zeros (AZ_DEP_EMB_ROWS)
   const void* q_w;     // bf16 A fragments of Wq, K dimension in the token accumulators' order
   const void* k_w;     // same for Wk
@@ -102,8 +98,6 @@ hipError_t az_launch_deployed_bf16(const AzDevNet& net, int boards, const float*
                                    int B, float* policy, float* value, float* wdl, hipStream_t stream);
 hipError_t az_launch_f32(const AzDevNet& net, const float* planes, const uint8_t* legal, int B,
                          float* policy, float* value, hipStream_t stream);
-// Boards per workgroup of a tiling (for grid sizing and tests).
-int az_mfma_boards_per_wg(int filters, int tiling);
 // Whether a tiling id (1 large, 2 small, 3 medium) exists for a filter count.
 bool az_mfma_tiling_valid(int filters, int tiling);
 // Whether an (dtype, filters) pair has MFMA kernels in the library.

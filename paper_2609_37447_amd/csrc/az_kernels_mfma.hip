@@ -971,12 +971,6 @@ bool az_mfma_supported(int dtype, int filters) {
   return (dtype >= 1 && dtype <= 3) && (filters == 64 || filters == 128 || filters == 256);
 }
 
-int az_mfma_boards_per_wg(int filters, int tiling) {
-  if (tiling == 2) return 1;
-  if (tiling == 3) return filters == 256 ? 1 : 2;
-  return filters == 256 ? 2 : 4;
-}
-
 bool az_mfma_tiling_valid(int filters, int tiling) {
   return tiling == 1 || tiling == 2 || (tiling == 3 && filters != 256);
 }

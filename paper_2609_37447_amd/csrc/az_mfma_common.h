@@ -50,7 +50,6 @@ template <> struct Mk<MK_F8> {
 };
 
 constexpr int cmax(int a, int b) { return a > b ? a : b; }
-constexpr int gcd_c(int a, int b) { return b == 0 ? a : gcd_c(b, a % b); }
 
 
 template <int I, int N, class F>

@@ -577,7 +577,7 @@ int az_net_load(const az_layer_spec* spec_in, const float* weights, size_t n_wei
   const int g = s.pool_every > 0 ? F / 4 : 0, Fr = F - g, V = s.value_channels, D = s.token_dim;
   std::vector<uint8_t> stem, tower, head, emb, qw, kw, pw;
   std::vector<float> bias, qhi, head_b, fc2w, head_sc, head_bc, fc1t;
-  std::vector<double> qmul, qbias, qres, qext, pool_m, pool_b, pool_cinv;
+  std::vector<double> qmul, qbias, qext, pool_m, pool_b, pool_cinv;
   std::vector<float> emb_sc, emb_bc, wfc1t;
   std::vector<float> pool_wt;
   std::vector<uint32_t> actions;
@@ -637,7 +637,7 @@ int az_net_load(const az_layer_spec* spec_in, const float* weights, size_t n_wei
         std::vector<double> a(act_scales, act_scales + K);
         qmul.resize((size_t)K * F);
         qbias.resize((size_t)K * F);
-        qres.assign(K, 0.0);
+        qext.assign((size_t)2 * K, 0.0);
         qhi.resize(K);
         for (int f = 0; f < F; ++f) {
           qmul[f] = 1.0 / a[0];
@@ -649,15 +649,11 @@ int az_net_load(const az_layer_spec* spec_in, const float* weights, size_t n_wei
             qbias[(size_t)(1 + n) * F + f] = (double)v.b[n][f] / a[n + 1];
           }
         for (int k = 0; k < K; ++k) {
-          if (k >= 2 && k % 2 == 0) qres[k] = a[k - 2] / a[k];
+          if (k >= 2 && k % 2 == 0) qext[2 * k] = a[k - 2] / a[k];
           // the largest code: min(qmax, cap / a[k]) rounded to the grid
           double c = s.act_cap > 0.0f ? (double)s.act_cap / a[k] : qmax;
           if (c > qmax) c = qmax;
           qhi[k] = dtype == AZ_INT8 ? (float)quant_i8(c) : e4m3_value(quant_e4m3(c));
-        }
-        qext.resize((size_t)2 * K);
-        for (int k = 0; k < K; ++k) {
-          qext[2 * k] = qres[k];
           qext[2 * k + 1] = qhi[k];
         }
       }
@@ -720,12 +716,11 @@ int az_net_load(const az_layer_spec* spec_in, const float* weights, size_t n_wei
 
   // One device allocation, 256-byte aligned sections.
   struct Sec { const void* src; size_t bytes; size_t off; };
-  const size_t VH = dep ? (size_t)V * 64 * H : (size_t)H * 64;
   std::vector<Sec> secs = {
       {stem.data(), stem.size(), 0}, {tower.data(), tower.size(), 0}, {head.data(), head.size(), 0},
       {bias.data(), bias.size() * 4, 0}, {qmul.data(), qmul.size() * 8, 0},
-      {qres.data(), qres.size() * 8, 0}, {qhi.data(), qhi.size() * 4, 0},
-      {head_b.data(), head_b.size() * 4, 0}, {dep ? nullptr : v.fc1_w, dep ? 0 : VH * 4, 0},
+      {qext.data(), qext.size() * 8, 0}, {qhi.data(), qhi.size() * 4, 0},
+      {head_b.data(), head_b.size() * 4, 0}, {qbias.data(), qbias.size() * 8, 0},
       {v.fc1_b, (size_t)H * 4, 0}, {dep ? (const void*)v.fc2_w : fc2w.data(), (dep ? 3 : 1) * (size_t)H * 4, 0},
       {head_sc.data(), head_sc.size() * 4, 0}, {head_bc.data(), head_bc.size() * 4, 0},
       {fc1t.data(), fc1t.size() * 4, 0},
@@ -735,8 +730,7 @@ int az_net_load(const az_layer_spec* spec_in, const float* weights, size_t n_wei
       {dep ? v.q_b : nullptr, dep ? (size_t)D * 4 : 0, 0}, {dep ? v.k_b : nullptr, dep ? (size_t)D * 4 : 0, 0},
       {pool_wt.data(), pool_wt.size() * 4, 0}, {pool_m.data(), pool_m.size() * 8, 0},
       {pool_b.data(), pool_b.size() * 8, 0}, {pool_cinv.data(), pool_cinv.size() * 8, 0},
-      {actions.data(), actions.size() * 4, 0}, {wfc1t.data(), wfc1t.size() * 4, 0},
-      {qbias.data(), qbias.size() * 8, 0}, {qext.data(), qext.size() * 8, 0}};
+      {actions.data(), actions.size() * 4, 0}, {wfc1t.data(), wfc1t.size() * 4, 0}};
   size_t total = 0;
   for (auto& sc : secs) { sc.off = total; total += align256(sc.bytes); }
 
@@ -774,18 +768,15 @@ int az_net_load(const az_layer_spec* spec_in, const float* weights, size_t n_wei
   d.value_hidden = H;
   d.value_conv_relu = s.value_conv_relu;
   d.act_cap = s.act_cap > 0.0f ? s.act_cap : INFINITY;
-  d.head_scale = hs;
   d.stem_w = at(0);
   d.tower_w = at(1);
   d.head_w = at(2);
   d.bias = atf(3);
   d.qmul = atd(4);
-  d.qres = atd(5);
+  d.qext = atd(5);
   d.qhi = atf(6);
-  d.qbias = atd(28);
-  d.qext = atd(29);
   d.head_b = atf(7);
-  d.fc1_w = atf(8);
+  d.qbias = atd(8);
   d.fc1_b = atf(9);
   d.fc2_w = atf(10);
   d.head_sc = atf(11);
