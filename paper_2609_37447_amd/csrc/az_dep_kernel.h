@@ -22,14 +22,15 @@
 //
 // What bounds it.  Large int8 batches: the wave's own instruction stream; its
 // float64 requantisation and the float64 conversions of it (2 to 3 times a plain
-// instruction) run with the matrix pipe idle, and 80 KB of weights a tap leave the
-// registers room for two steps of prefetch.  Small batches: that and the layers'
-// chain of barriers.  Measured on 14x160 against one-tap-at-a-time K loops and one
-// board per workgroup (us per batch): int8 64 boards 143 -> 140, 256 152 -> 143, 333
-// 290 -> 200, 512 298 -> 228, 1,024 382 -> 365; bf16 64 boards 211 -> 204, 333
-// 427 -> 293, 1,024 888 -> 670.  Four int8 boards per workgroup were slower than a
-// wave per board (1,024 boards 463 against 365: the epilogue of 160 values a lane
-// behind one barrier; its registers spill in the pooling layers).
+// instruction) run with the matrix pipe idle, and beside 160 accumulators a lane the
+// registers have room for a ring of three weight steps (5 KB each, 32 channels of a
+// tap).  Small batches: that and the layers' chain of barriers.  Measured on 14x160
+// against one-tap-at-a-time K loops and one board per workgroup, both on one box (us
+// per batch): int8 64 boards 143 -> 139, 256 146 -> 142, 333 285 -> 197, 512 289 ->
+// 212, 1,024 383 -> 366; bf16 64 boards 211 -> 203, 333 437 -> 293, 1,024 925 -> 713.
+// Four int8 boards per workgroup were slower than a wave per board (1,024 boards 463
+// against 365: the epilogue of 160 values a lane behind one barrier; its registers
+// spill in the pooling layers).
 //
 // Global pooling (every pool_every-th block).  After the first convolution's
 // K loop, the pooled channels (the last F/4) are transposed through LDS (int8:

@@ -40,7 +40,7 @@
 // What bounds it: the six products (27.6k MFMA cycles a 128-filter convolution on
 // the one compute unit a board has, 0.46 ms for 20x128) and, on small networks, the
 // latency of the layers' chain.  20x128, 64 boards: 13.5 ms -> 0.68 ms; 2x32, 16
-// boards: 100 -> 19.6 us; 1,024 boards: 343 -> 79 us; 2x256, 16 boards: 5.7 -> 0.27 ms.
+// boards: 102 -> 19.6 us; 1,024 boards: 355 -> 78 us; 2x256, 16 boards: 5.7 -> 0.27 ms.
 #include "az_internal.h"
 #include "az_mfma_common.h"
 

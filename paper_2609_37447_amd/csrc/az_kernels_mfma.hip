@@ -36,14 +36,15 @@
 // per-channel constants are staged through LDS one layer ahead.
 //
 // What bounds it.  With every compute unit busy (1,024 boards) the chip's clock: at
-// 20x128 int8 the batch takes 281 us against 238 us for 768 boards, the same work
-// per compute unit (a loop of nothing but these MFMAs runs at 1.93 GHz on all 256
-// compute units, 2.3 GHz on half of them).  Below that, the float64 epilogue: a wave
-// has a SIMD to itself and issues it between products of the next block (the tail)
-// or after the loop.  Against the K loop in tap order (each fragment read for one
-// product, two waves streaming the same weights) the batch went from 314-327 us to
-// 270-281 us, bf16 from 554 to 467, 24x256 bf16 from 2,529 to 2,351 (large tiling)
-// and from 917 to 540 at 64 boards.
+// 20x128 int8 the batch takes 254 us against 235 us for 768 boards, the same work
+// per compute unit, on one box (281 against 238 on a box that clocks lower); a loop of
+// nothing but these MFMAs runs at 1.93 GHz on all 256 compute units, 2.3 GHz on half
+// of them.  Below that, the float64 epilogue: a wave has a SIMD to itself and issues
+// it between products of the next block (the tail) or after the loop.  Against the K
+// loop in tap order (each fragment read for one product, two waves streaming the same
+// weights), both on one box, us: 20x128 int8 64 boards 90 -> 85, 1,024 299 -> 254;
+// bf16 32 boards 143 -> 130, 256 182 -> 161, 1,024 553 -> 465; 24x256 bf16 64 boards
+// 920 -> 540, 1,024 2,500 -> 2,338.
 //
 // Activation layout in LDS: [board group][row][board][column][channel], one run
 // of F channels per square, stored in 16-byte chunks whose position is

@@ -467,8 +467,8 @@ def test_graph_capture_replays_match_eager():
 
 @pytest.mark.parametrize("filters,blocks", [(64, 2), (256, 1)])
 def test_f32_wide_networks(filters, blocks):
-    # wider fp32 nets: the convolution weights no longer fit the LDS staging area
-    # (global-memory path), and at 256 filters the LDS budget is at its largest
+    # wider fp32 nets: the wave tile of 64 filters, and at 256 filters the widest one
+    # and the largest LDS
     shape = azgen.NetShape(in_planes=20, blocks=blocks, filters=filters, policy_planes=73, value_hidden=64,
                            act_cap=6.0, value_conv_relu=1)
     blob = azgen.make_weights(shape, 880 + filters, alpha_fold=True, bf16=False)
