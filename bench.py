@@ -71,18 +71,18 @@ def kernel_sha(shape, dtype):
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
 # (workload, tiling, batch): (kernel_sha, FETCH_SIZE KiB, WRITE_SIZE KiB, MFMA busy fraction)
 COUNTERS = {
-    ("net20x128_int8_b1024", 1, 1024): ("f3d1ea1427b3ea1e798d96c1f19dadedeb5c17cff4c87c38eae7b0ff52a63e09", 29184.3, 18696.0, 0.5860),
-    ("net20x128_int8_b1024", 3, 1024): ("f3d1ea1427b3ea1e798d96c1f19dadedeb5c17cff4c87c38eae7b0ff52a63e09", 44332.1, 18704.0, 0.6655),
-    ("net20x128_int8_b1024", 2, 64): ("f3d1ea1427b3ea1e798d96c1f19dadedeb5c17cff4c87c38eae7b0ff52a63e09", 24370.8, 1170.0, 0.1051),
-    ("net20x128_bf16_b1024", 1, 1024): ("f3d1ea1427b3ea1e798d96c1f19dadedeb5c17cff4c87c38eae7b0ff52a63e09", 52070.3, 18696.0, 0.7210),
-    ("net20x128_bf16_b256", 2, 256): ("f3d1ea1427b3ea1e798d96c1f19dadedeb5c17cff4c87c38eae7b0ff52a63e09", 48110.3, 4680.0, 0.5974),
-    ("net20x128_bf16_b32", 2, 32): ("f3d1ea1427b3ea1e798d96c1f19dadedeb5c17cff4c87c38eae7b0ff52a63e09", 47032.3, 585.0, 0.0704),
-    ("net20x128_fp8_b1024", 1, 1024): ("f3d1ea1427b3ea1e798d96c1f19dadedeb5c17cff4c87c38eae7b0ff52a63e09", 29243.8, 18696.0, 0.4719),
-    ("net24x256_bf16_b1024", 1, 1024): ("f3d1ea1427b3ea1e798d96c1f19dadedeb5c17cff4c87c38eae7b0ff52a63e09", 450562.8, 18704.1, 0.8273),
-    ("deployed14x160_int8_b1024", 1, 1024): ("fc736842338dfe2064cd505dac3abeef8a7968170061d8a6636ae6df55049899", 35423.5, 7552.0, 0.4916),
-    ("deployed14x160_int8_b1024", 2, 64): ("fc736842338dfe2064cd505dac3abeef8a7968170061d8a6636ae6df55049899", 29223.9, 472.0, 0.0732),
-    ("deployed14x160_bf16_b1024", 1, 1024): ("fc736842338dfe2064cd505dac3abeef8a7968170061d8a6636ae6df55049899", 114946.9, 7536.0, 0.5637),
-    ("tiny_2x32_f32_b16", 0, 16): ("1aa299be26c797c412efab26d28cfe7012f75cfb22005dbb3afff0d58b7a026b", 1416.0, 292.5, 0.0078),
+    ("net20x128_int8_b1024", 1, 1024): ("5d000009e49ce00a37cbf0975c6145516eaf6fd8bc6a2fa4884fbe4e468cf44a", 29184.8, 18696.0, 0.5836),
+    ("net20x128_int8_b1024", 3, 1024): ("5d000009e49ce00a37cbf0975c6145516eaf6fd8bc6a2fa4884fbe4e468cf44a", 44314.9, 18704.0, 0.6621),
+    ("net20x128_int8_b1024", 2, 64): ("5d000009e49ce00a37cbf0975c6145516eaf6fd8bc6a2fa4884fbe4e468cf44a", 24371.3, 1170.0, 0.1056),
+    ("net20x128_bf16_b1024", 1, 1024): ("5d000009e49ce00a37cbf0975c6145516eaf6fd8bc6a2fa4884fbe4e468cf44a", 52071.3, 18696.0, 0.7171),
+    ("net20x128_bf16_b256", 2, 256): ("5d000009e49ce00a37cbf0975c6145516eaf6fd8bc6a2fa4884fbe4e468cf44a", 48108.8, 4680.0, 0.5966),
+    ("net20x128_bf16_b32", 2, 32): ("5d000009e49ce00a37cbf0975c6145516eaf6fd8bc6a2fa4884fbe4e468cf44a", 47030.8, 585.0, 0.0705),
+    ("net20x128_fp8_b1024", 1, 1024): ("5d000009e49ce00a37cbf0975c6145516eaf6fd8bc6a2fa4884fbe4e468cf44a", 29244.3, 18696.0, 0.4709),
+    ("net24x256_bf16_b1024", 1, 1024): ("5d000009e49ce00a37cbf0975c6145516eaf6fd8bc6a2fa4884fbe4e468cf44a", 450559.3, 18704.1, 0.8273),
+    ("deployed14x160_int8_b1024", 1, 1024): ("3ed7c146ea2a960e4d467bfca45cf8db96c307f42280268bac04592e2840db97", 35439.0, 7552.0, 0.4869),
+    ("deployed14x160_int8_b1024", 2, 64): ("3ed7c146ea2a960e4d467bfca45cf8db96c307f42280268bac04592e2840db97", 29231.9, 472.0, 0.0732),
+    ("deployed14x160_bf16_b1024", 1, 1024): ("3ed7c146ea2a960e4d467bfca45cf8db96c307f42280268bac04592e2840db97", 114954.9, 7536.0, 0.5580),
+    ("tiny_2x32_f32_b16", 0, 16): ("6ea7086f1dece27356e6ac9361f30c0f146457a1c02423a2379f9279fb02cfd0", 1428.5, 292.5, 0.0076),
 }
 
 # MI355X published dense peaks (FLOP/s) at 2.4 GHz, 256 CUs.
