@@ -25,7 +25,7 @@
 // vertical taps (block b's neighbour rows are block b +- 1).  A wave owns MB
 // channel blocks x NB square blocks, chosen so that one pass covers the layer:
 // 1 x 1 up to 16 filters, 1 x 2 up to 64, 1 x 4 up to 128, 2 x 4 up to 256 (32
-// filters: 1 x 1 20.7 us, 1 x 2 19.6 us; 64: 1 x 2 33 us, 1 x 4 36 us: the waves that
+// filters: 1 x 1 20.7 us, 1 x 2 19.3 us; 64: 1 x 2 33 us, 1 x 4 36 us: the waves that
 // share a channel block each stream its weights through the L1).  The 2 x 4 tile does
 // not fit the 256 registers two waves a SIMD leave each: 53 of them spill, 216 bytes
 // of scratch a lane, on every network above 128 filters.
@@ -40,7 +40,7 @@
 // What bounds it: the six products (27.6k MFMA cycles a 128-filter convolution on
 // the one compute unit a board has, 0.46 ms for 20x128) and, on small networks, the
 // latency of the layers' chain.  20x128, 64 boards: 13.5 ms -> 0.68 ms; 2x32, 16
-// boards: 102 -> 19.6 us; 1,024 boards: 355 -> 78 us; 2x256, 16 boards: 5.7 -> 0.27 ms.
+// boards: 102 -> 19.3 us; 1,024 boards: 355 -> 78 us; 2x256, 16 boards: 5.7 -> 0.27 ms.
 #include "az_internal.h"
 #include "az_mfma_common.h"
 
@@ -250,10 +250,11 @@ __global__ __launch_bounds__(NT) void az_net_f32_kernel(AzDevNet p, const float*
             }
           }
       };
-      // checked once for the wave's values: a check in every split costs 2 to 4% of
-      // the network
-      if (__builtin_expect(__any(most >= BIG), 0)) store([](float x, uint32_t& h, uint32_t& m, uint32_t& l) { split3(x, h, m, l); });
-      else store([](float x, uint32_t& h, uint32_t& m, uint32_t& l) { split3_small(x, h, m, l); });
+      // checked once for the wave's values, off the stores' path: a check in every
+      // split costs 2 to 4% of the network
+      store([](float x, uint32_t& h, uint32_t& m, uint32_t& l) { split3_small(x, h, m, l); });
+      if (__builtin_expect(__any(most >= BIG), 0))
+        store([](float x, uint32_t& h, uint32_t& m, uint32_t& l) { split3(x, h, m, l); });
     }
     __syncthreads();
   };
