@@ -71,18 +71,18 @@ def kernel_sha(shape, dtype):
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
 # (workload, tiling, batch): (kernel_sha, FETCH_SIZE KiB, WRITE_SIZE KiB, MFMA busy fraction)
 COUNTERS = {
-    ("net20x128_int8_b1024", 1, 1024): ("5d000009e49ce00a37cbf0975c6145516eaf6fd8bc6a2fa4884fbe4e468cf44a", 29184.8, 18696.0, 0.5836),
-    ("net20x128_int8_b1024", 3, 1024): ("5d000009e49ce00a37cbf0975c6145516eaf6fd8bc6a2fa4884fbe4e468cf44a", 44314.9, 18704.0, 0.6621),
-    ("net20x128_int8_b1024", 2, 64): ("5d000009e49ce00a37cbf0975c6145516eaf6fd8bc6a2fa4884fbe4e468cf44a", 24371.3, 1170.0, 0.1056),
-    ("net20x128_bf16_b1024", 1, 1024): ("5d000009e49ce00a37cbf0975c6145516eaf6fd8bc6a2fa4884fbe4e468cf44a", 52071.3, 18696.0, 0.7171),
-    ("net20x128_bf16_b256", 2, 256): ("5d000009e49ce00a37cbf0975c6145516eaf6fd8bc6a2fa4884fbe4e468cf44a", 48108.8, 4680.0, 0.5966),
-    ("net20x128_bf16_b32", 2, 32): ("5d000009e49ce00a37cbf0975c6145516eaf6fd8bc6a2fa4884fbe4e468cf44a", 47030.8, 585.0, 0.0705),
-    ("net20x128_fp8_b1024", 1, 1024): ("5d000009e49ce00a37cbf0975c6145516eaf6fd8bc6a2fa4884fbe4e468cf44a", 29244.3, 18696.0, 0.4709),
-    ("net24x256_bf16_b1024", 1, 1024): ("5d000009e49ce00a37cbf0975c6145516eaf6fd8bc6a2fa4884fbe4e468cf44a", 450559.3, 18704.1, 0.8273),
-    ("deployed14x160_int8_b1024", 1, 1024): ("3ed7c146ea2a960e4d467bfca45cf8db96c307f42280268bac04592e2840db97", 35439.0, 7552.0, 0.4869),
-    ("deployed14x160_int8_b1024", 2, 64): ("3ed7c146ea2a960e4d467bfca45cf8db96c307f42280268bac04592e2840db97", 29231.9, 472.0, 0.0732),
-    ("deployed14x160_bf16_b1024", 1, 1024): ("3ed7c146ea2a960e4d467bfca45cf8db96c307f42280268bac04592e2840db97", 114954.9, 7536.0, 0.5580),
-    ("tiny_2x32_f32_b16", 0, 16): ("6ea7086f1dece27356e6ac9361f30c0f146457a1c02423a2379f9279fb02cfd0", 1428.5, 292.5, 0.0076),
+    ("net20x128_int8_b1024", 1, 1024): ("0e5d69ddf4a78374b3d9f5a471aa3482677366b0738468725eaaeb075aeb2dea", 29184.8, 18696.0, 0.5854),
+    ("net20x128_int8_b1024", 3, 1024): ("0e5d69ddf4a78374b3d9f5a471aa3482677366b0738468725eaaeb075aeb2dea", 44164.6, 18704.0, 0.6642),
+    ("net20x128_int8_b1024", 2, 64): ("0e5d69ddf4a78374b3d9f5a471aa3482677366b0738468725eaaeb075aeb2dea", 24371.3, 1170.0, 0.1055),
+    ("net20x128_bf16_b1024", 1, 1024): ("0e5d69ddf4a78374b3d9f5a471aa3482677366b0738468725eaaeb075aeb2dea", 52071.3, 18696.0, 0.7192),
+    ("net20x128_bf16_b256", 2, 256): ("0e5d69ddf4a78374b3d9f5a471aa3482677366b0738468725eaaeb075aeb2dea", 48108.8, 4680.0, 0.5981),
+    ("net20x128_bf16_b32", 2, 32): ("0e5d69ddf4a78374b3d9f5a471aa3482677366b0738468725eaaeb075aeb2dea", 47030.8, 585.0, 0.0705),
+    ("net20x128_fp8_b1024", 1, 1024): ("0e5d69ddf4a78374b3d9f5a471aa3482677366b0738468725eaaeb075aeb2dea", 29244.3, 18696.0, 0.4717),
+    ("net24x256_bf16_b1024", 1, 1024): ("0e5d69ddf4a78374b3d9f5a471aa3482677366b0738468725eaaeb075aeb2dea", 450559.3, 18704.0, 0.8241),
+    ("deployed14x160_int8_b1024", 1, 1024): ("8bb52f3098b9a0499bf1ae4f84bf32aae8eedd9e29d06231198971a655f31af5", 35439.0, 7552.0, 0.4904),
+    ("deployed14x160_int8_b1024", 2, 64): ("8bb52f3098b9a0499bf1ae4f84bf32aae8eedd9e29d06231198971a655f31af5", 29231.9, 472.0, 0.0731),
+    ("deployed14x160_bf16_b1024", 1, 1024): ("8bb52f3098b9a0499bf1ae4f84bf32aae8eedd9e29d06231198971a655f31af5", 114954.9, 7536.0, 0.5593),
+    ("tiny_2x32_f32_b16", 0, 16): ("c5f3c835a4c279637153a0b1fd604476bf18452ea7dd08ad30dbd3e1dac618cb", 1428.0, 292.5, 0.0079),
 }
 
 # MI355X published dense peaks (FLOP/s) at 2.4 GHz, 256 CUs.

@@ -42,8 +42,8 @@ struct AzDevNet {
   // qext[2k], qext[2k + 1] = qres[k], qhi[k] side by side, for kernels that stage
   // them with the per-channel constants; qres[k] = a[k-2] / a[k] for the second conv
   // of a block (its residual input's code scaled into the output's code units).
-  const float* qhi;
   const double* qext;
+  const float* qhi;
   const float* head_b;  // [AZ_HEAD_ROWS]: policy biases, value conv bias at row P, zeros
   const float* fc1_b;   // [H]
   const float* fc2_w;   // [H]
