@@ -234,10 +234,10 @@ int az_net_moves(const az_net* net);
  * network has two to choose from: 1, one wave per board, four per compute unit
  * (AZ_INT8), or two boards per workgroup of four waves (AZ_BF16); 2, four waves
  * per board.  A tiling other than 0 runs for every B.  Every tiling computes
- * bitwise the same results (for finite weights: the four-board tilings leave out
- * the products of a weight and a row outside the board, where an infinity times
- * zero would be NaN).  AZ_F32 has a single tiling and accepts only 0.
- * Returns AZ_OK or AZ_ERR_INVALID_ARG. */
+ * bitwise the same results (for finite weights: the large tiling of F = 128
+ * leaves out the products of a weight and a row outside the board, where an
+ * infinity times zero would be NaN).  AZ_F32 has a single tiling and accepts only
+ * 0.  Returns AZ_OK or AZ_ERR_INVALID_ARG. */
 int az_net_set_tiling(az_net* net, int32_t tiling);
 
 /* The tiling az_eval_batch runs for a batch of B (1, 2 or 3; 0 for AZ_F32), or
